@@ -1,11 +1,11 @@
 // LUT weight packing on gfx950 (offline; the decode-side weight format).
 //
-// PER_ROW (benchmark decode format): one workgroup per output row sorts the
-// row in LDS (bitonic sort of order-preserving integer keys), sums each of the
-// 2^b equal-count bins in double-double arithmetic, divides by the count in
-// fp64 and rounds once to fp16 (nearest even).  Codes are the nearest entry,
-// ties to the lower index, decided by exact fp64 comparisons with the
-// midpoints of adjacent entries.
+// PER_ROW (benchmark decode format): one workgroup per output row finds the
+// boundaries of the 2^b equal-count bins of the sorted row (by selection, not
+// by sorting), sums each bin in double-double arithmetic, divides by the count
+// in fp64 and rounds once to fp16 (nearest even).  Codes are the nearest entry,
+// ties to the lower index, by exact comparisons with the midpoints of adjacent
+// entries.
 //
 // PAPER_GRID (paper App. A "LUT formats"): the NVFP4 two-level scaling with a
 // signed E4M3 block scale that carries the sign of the block's
@@ -77,15 +77,6 @@ __device__ inline void dd_add(double& hi, double& lo, double x) {
   lo += e;
 }
 
-__device__ inline void dd_merge(double& h1, double& l1, double h2, double l2) {
-  double s, e;
-  two_sum(h1, h2, s, e);
-  e += l1 + l2;
-  const double t = s + e;          // fast two-sum normalization (|s| >= |e|)
-  l1 = e - (t - s);
-  h1 = t;
-}
-
 // code bits of 32 codes of one group into the dword layout of dq.h
 template <int BITS>
 __device__ inline void put_code(uint32_t (&w)[3], int t, uint32_t c) {
@@ -113,89 +104,381 @@ __device__ inline void store_group(uint8_t* codes, int64_t row, int64_t group, i
 }
 
 // ---------------------------------------------------------------- PER_ROW
-template <int BITS>
-__global__ __launch_bounds__(1024) void pack_lut_per_row_kernel(const float* __restrict__ W, int64_t N, int64_t K,
-                                                                int64_t P, int64_t KC, uint8_t* __restrict__ codes,
-                                                                uint16_t* __restrict__ lut) {
-  constexpr int NB = 1 << BITS;
-  extern __shared__ __align__(16) uint8_t smem[];
-  uint32_t* keys = reinterpret_cast<uint32_t*>(smem);
-  __shared__ double part_hi[1024], part_lo[1024];
-  __shared__ double mids[NB];
+// One workgroup of T threads per row, the row in registers (E4 float4 per
+// thread).  The equal-count bins need the row's 2^b - 1 values at the sorted
+// positions j K / 2^b (thresholds T_j), not the sorted row:
+//  1. a histogram of 2048 equal-width buckets over +-2.5 mean|w| (a monotone
+//     map of the value, the ends open) and its prefix sums give the bucket of
+//     every threshold and the class #{j : w >= T_j} of all other buckets;
+//  2. each value looks its bucket up: it is added to its thread's own
+//     double-double sum of its class in LDS (lane-contiguous, no bank
+//     conflict), or, from a threshold's bucket (about 0.5 % of a Gaussian
+//     row), goes to that bucket's list;
+//  3. a wavefront ranks each threshold in its bucket's list; a crowded bucket,
+//     of more than kCap members (few distinct values, extreme tails), is
+//     bisected instead, bit by bit over the keys below the common prefix of
+//     its members (none when they are all equal).  The values of these
+//     buckets join the sums, which are merged in a fixed order.  Values equal to a threshold
+//     that belong below it are moved by count: bin j = class j + d_{j+1}
+//     T_{j+1} - d_j T_j, with d_j = j K / 2^b minus the number of values
+//     below T_j (each product is exact in fp64);
+//  4. codes by comparison with the midpoints rounded down to fp32 (for an
+//     fp32 w the same as the exact fp64 comparison), eight lanes combining
+//     their four codes each into a 32-code group.
+// Bound: the VALU (about 78 instructions per value) and the LDS accesses
+// beside it; the row is read once.  A bitonic sort of the row in LDS (78
+// passes at K = 4096) took 1417 us for 12288 x 4096, this takes 157
+// (1.4 TB/s; 475 with weights of few distinct values).  Thresholds by comparison for every value, four wavefronts per row instead
+// of two and a full double-double merge took 207.  The 16 rows of a tile run
+// on one XCD, so that their 12-byte groups merge into whole lines in its L2.
+constexpr int kBuckets = 2048;
+constexpr int kCap = 128;   // members of a threshold's bucket that are listed and ranked
 
-  const int64_t row = blockIdx.x;
-  const int tid = threadIdx.x, T = blockDim.x;
-  const int64_t groups = KC * 4;
+template <int BITS, int T>
+constexpr size_t pack_rows_lds() {   // the class sums; the histogram before them
+  constexpr size_t sums = (size_t)(1 << BITS) * T * 16, hist = (size_t)kBuckets * 4;
+  return sums > hist ? sums : hist;
+}
+
+// largest fp32 not above d
+__device__ inline float f64_to_f32_down(double d) {
+  const float f = (float)d;
+  if (!((double)f > d)) return f;
+  const uint32_t b = __float_as_uint(f);
+  return __uint_as_float((b & 0x7FFFFFFFu) == 0u ? 0x80000001u : (b & 0x80000000u) ? b + 1u : b - 1u);
+}
+
+// #{j : x > m[j]}, m ascending
+template <int NT>
+__device__ inline uint32_t code_of(float x, const float (&m)[NT]) {
+  if constexpr (NT == 7) {
+    const bool b2 = x > m[3];
+    const bool b1 = x > (b2 ? m[5] : m[1]);
+    const float lo = b1 ? m[2] : m[0], hi = b1 ? m[6] : m[4];
+    const bool b0 = x > (b2 ? hi : lo);
+    return (b2 ? 4u : 0u) + (b1 ? 2u : 0u) + (b0 ? 1u : 0u);
+  } else {
+    const bool b1 = x > m[1];
+    const bool b0 = x > (b1 ? m[2] : m[0]);
+    return (b1 ? 2u : 0u) + (b0 ? 1u : 0u);
+  }
+}
+
+template <int BITS, int T, int E4>
+__global__ __launch_bounds__(T) void pack_lut_per_row_kernel(const float* __restrict__ W, int64_t N, int64_t tiles,
+                                                             int K, int KC, uint8_t* __restrict__ codes,
+                                                             uint16_t* __restrict__ lut) {
+  constexpr int NB = 1 << BITS, NT = NB - 1, NW = T / 64, BPT = kBuckets / T;
+  constexpr int GB = BITS == 3 ? 12 : 8;
+  extern __shared__ __align__(16) uint8_t smem[];
+  uint32_t* hist = reinterpret_cast<uint32_t*>(smem);
+  double2* sums = reinterpret_cast<double2*>(smem);          // [NB][T], once the histogram has been scanned
+  // class, or the bucket's first threshold + 0x80 (listed) or + 0xC0 (crowded)
+  __shared__ uint8_t s_mark[kBuckets];
+  __shared__ uint32_t s_cand[NT][kCap];
+  __shared__ float s_f[NW];
+  __shared__ uint32_t s_w[2][NW];
+  __shared__ int s_slot[NT], s_lo[NT], s_cnt[NT], s_fill[NT], s_less[NT];
+  __shared__ uint32_t s_key[NT], s_min[NT], s_max[NT];
+  __shared__ double s_hi[NB], s_lo2[NB];
+  __shared__ uint16_t s_entry[NB];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // workgroup b runs on XCD b % 8: tile = 8 (b / 128) + b % 8, row (b / 8) % 16 of it
+  const int64_t tile = (int64_t)(blockIdx.x >> 7) * 8 + (blockIdx.x & 7);
+  if (tile >= tiles) return;
+  const int ri = (int)((blockIdx.x >> 3) & 15);
+  const int64_t row = tile * 16 + ri;
+  const int sub = tid & 7;
+  // dword `sub` of group g of this row
+  auto code_dword = [&](int g) {
+    return reinterpret_cast<uint32_t*>(codes + ((tile * KC + (g >> 2)) * 64 + (g & 3) * 16 + ri) * GB) + sub;
+  };
   if (row >= N) {   // padding rows of the last 16-row tile: zero codes and entries
-    const uint32_t z[3] = {0u, 0u, 0u};
-    for (int64_t g = tid; g < groups; g += T) store_group<BITS>(codes, row, g, KC, z);
+    for (int q = tid; q < KC * 32; q += T)
+      if (sub < GB / 4) *code_dword(q >> 3) = 0u;
     if (tid < NB) lut[row * NB + tid] = 0;
     return;
   }
-  const float* wr = W + row * K;
-  for (int64_t k = tid; k < P; k += T) keys[k] = k < K ? sort_key(wr[k]) : 0xFFFFFFFFu;
+
+  // ---- the row (quad q = tid + e T: columns 4q .. 4q + 3), sum |w|
+  const float4_t* wr = reinterpret_cast<const float4_t*>(W + row * K);
+  const int nq = K / 4;   // K % 32 == 0
+  float v[E4][4];
+  float s = 0.0f;
+#pragma unroll
+  for (int e = 0; e < E4; ++e) {
+    const int q = tid + e * T;
+    const float4_t x = q < nq ? wr[q] : float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[e][t] = x[t];
+  }
+#pragma unroll
+  for (int i = 0; i < BPT; ++i) hist[tid + i * T] = 0u;
+#pragma unroll
+  for (int e = 0; e < E4; ++e)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) s += fabsf(v[e][t]);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (lane == 0) s_f[wave] = s;
+  if (tid < NT) {
+    s_slot[tid] = s_lo[tid] = s_less[tid] = 0;
+    s_cnt[tid] = s_fill[tid] = 0;
+    s_key[tid] = s_max[tid] = 0u;
+    s_min[tid] = 0xFFFFFFFFu;
+  }
   __syncthreads();
-  // bitonic sort, ascending
-  for (int64_t kk = 2; kk <= P; kk <<= 1) {
-    for (int64_t jj = kk >> 1; jj > 0; jj >>= 1) {
-      for (int64_t t = tid; t < P / 2; t += T) {
-        const int64_t a = 2 * t - (t & (jj - 1));
-        const int64_t b = a + jj;
-        const uint32_t ka = keys[a], kb = keys[b];
-        const bool up = (a & kk) == 0;
-        if ((ka > kb) == up) {
-          keys[a] = kb;
-          keys[b] = ka;
+  float total = 0.0f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) total += s_f[w];
+  const float scale = fminf(1e30f, (kBuckets / 5.0f) / (total / (float)K));
+  auto bucket = [&](float x) {   // non-decreasing in x
+    return (int)__builtin_amdgcn_fmed3f(__builtin_fmaf(x, scale, 0.5f * kBuckets), 0.0f, (float)(kBuckets - 1));
+  };
+
+  // ---- 1. histogram, prefix sums, marks
+#pragma unroll
+  for (int e = 0; e < E4; ++e)
+    if (tid + e * T < nq)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) atomicAdd(&hist[bucket(v[e][t])], 1u);
+  __syncthreads();
+  const int cnt = K / NB;
+  {
+    uint32_t h[BPT];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) mine += h[i] = hist[tid * BPT + i];
+    uint32_t incl = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t o = (uint32_t)__shfl_up((int)incl, off, 64);
+      if (lane >= off) incl += o;
+    }
+    if (lane == 63) s_w[0][wave] = incl;
+    __syncthreads();
+    uint32_t lo = incl - mine;
+    for (int w = 0; w < wave; ++w) lo += s_w[0][w];
+    int j = 1;   // the next threshold at or past this position
+    while (j <= NT && (uint32_t)(j * cnt) < lo) ++j;
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+      uint32_t mark = (uint32_t)(j - 1);   // thresholds below the bucket
+      const int first = j;
+      for (; j <= NT && (uint32_t)(j * cnt) < lo + h[i]; ++j) {
+        mark = (h[i] > (uint32_t)kCap ? 0xC0u : 0x80u) + (uint32_t)(first - 1);
+        s_slot[j - 1] = first - 1;
+        s_lo[j - 1] = (int)lo;
+        s_less[j - 1] = (int)lo;
+        s_cnt[j - 1] = (int)h[i];
+      }
+      s_mark[tid * BPT + i] = (uint8_t)mark;
+      lo += h[i];
+    }
+  }
+  __syncthreads();
+
+  // ---- 2. class sums, and the members of the marked buckets
+#pragma unroll
+  for (int c = 0; c < NB; ++c) sums[c * T + tid] = double2{0.0, 0.0};
+  auto add = [&](int c, float x) {
+    double2 a = sums[c * T + tid];
+    dd_add(a.x, a.y, (double)x);
+    sums[c * T + tid] = a;
+  };
+#pragma unroll
+  for (int e = 0; e < E4; ++e)
+    if (tid + e * T < nq)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const uint32_t m = s_mark[bucket(v[e][t])];
+        if (m & 0x80u) {
+          const uint32_t key = sort_key(v[e][t]);
+          if (m & 0x40u) {
+            atomicMin(&s_min[m & 7u], key);
+            atomicMax(&s_max[m & 7u], key);
+          } else {
+            const int p = atomicAdd(&s_fill[m & 7u], 1);
+            if (p < kCap) s_cand[m & 7u][p] = key;   // always, for finite values
+          }
         }
+        add((int)(m & 7u), (m & 0x80u) ? 0.0f : v[e][t]);
+      }
+  __syncthreads();
+
+  // ---- 3. thresholds
+  bool listed = true;   // every marked bucket fits its list
+  for (int j = 0; j < NT; ++j) listed = listed && s_cnt[j] <= kCap;
+  for (int j = wave; j < NT; j += NW) {
+    const int n = s_cnt[j], rank = (j + 1) * cnt - s_lo[j];
+    if (n > kCap) continue;
+    const uint32_t* c = s_cand[s_slot[j]];
+    for (int c0 = 0; c0 < n; c0 += 64) {
+      const bool in = c0 + lane < n;
+      const uint32_t key = in ? c[c0 + lane] : 0u;
+      int less = 0, same = 0;
+      for (int i = 0; i < n; ++i) {
+        const uint32_t o = c[i];
+        less += o < key ? 1 : 0;
+        same += o == key ? 1 : 0;
+      }
+      if (in && less <= rank && rank < less + same) {   // every lane that holds the value
+        s_key[j] = key;
+        s_less[j] = s_lo[j] + less;
+      }
+    }
+  }
+  if (!listed) {
+    for (int j = 0; j < NT; ++j) {
+      if (s_cnt[j] <= kCap) continue;   // uniform over the workgroup
+      // the largest key with at most (j + 1) cnt keys below it, from the
+      // common prefix of the bucket's members down
+      const uint32_t differ = s_min[s_slot[j]] ^ s_max[s_slot[j]];
+      const int bits = differ == 0u ? 0 : 32 - __clz((int)differ);
+      uint32_t key = bits == 32 ? 0u : s_min[s_slot[j]] >> bits << bits;
+      int less = s_lo[j];
+      for (int bit = bits - 1; bit >= 0; --bit) {
+        const uint32_t trial = key | (1u << bit);
+        uint32_t below = 0;
+#pragma unroll
+        for (int e = 0; e < E4; ++e)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            below += (uint32_t)__popcll(__ballot(tid + e * T < nq && sort_key(v[e][t]) < trial));
+        if (lane == 0) s_w[bit & 1][wave] = below;
+        __syncthreads();
+        below = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) below += s_w[bit & 1][w];
+        if ((int)below <= (j + 1) * cnt) {
+          key = trial;
+          less = (int)below;
+        }
+      }
+      if (tid == 0) {
+        s_key[j] = key;
+        s_less[j] = less;
       }
       __syncthreads();
     }
   }
-  // bin sums: T/NB threads per bin
-  const int64_t cnt = K / NB;
-  const int per = T / NB;
-  const int bin = tid / per, sub = tid % per;
-  double hi = 0.0, lo = 0.0;
-  for (int64_t k = sub; k < cnt; k += per) dd_add(hi, lo, (double)key_value(keys[bin * cnt + k]));
-  part_hi[tid] = hi;
-  part_lo[tid] = lo;
   __syncthreads();
-  for (int off = per / 2; off > 0; off >>= 1) {
-    if (sub < off) {
-      double h = part_hi[tid], l = part_lo[tid];
-      dd_merge(h, l, part_hi[tid + off], part_lo[tid + off]);
-      part_hi[tid] = h;
-      part_lo[tid] = l;
-    }
-    __syncthreads();
-  }
-  __shared__ uint16_t entries[NB];
-  if (tid < NB) {
-    double h = part_hi[tid * per], l = part_lo[tid * per];
-    const double sum = h + l;                 // already normalized: h == RN(h + l)
-    const uint16_t e = f64_to_f16_rne(sum / (double)cnt);
-    entries[tid] = e;
-    lut[row * NB + tid] = e;
-  }
-  __syncthreads();
-  if (tid < NB - 1) mids[tid] = (f16_bits_to_f64(entries[tid]) + f16_bits_to_f64(entries[tid + 1])) * 0.5;
-  __syncthreads();
-  // codes, one 32-column group per thread iteration
-  for (int64_t g = tid; g < groups; g += T) {
-    uint32_t w[3] = {0u, 0u, 0u};
-    const int64_t kbase = g * 32;
-    for (int t = 0; t < 32; ++t) {
-      const int64_t k = kbase + t;
-      if (k < K) {
-        const double v = (double)wr[k];
-        uint32_t c = 0;
+  // the members of the marked buckets join their classes
+  auto class_of = [&](uint32_t key) {
+    int c = 0;
 #pragma unroll
-        for (int m = 0; m < NB - 1; ++m) c += v > mids[m] ? 1u : 0u;
-        put_code<BITS>(w, t, c);
-      }
-    }
-    store_group<BITS>(codes, row, g, KC, w);
+    for (int j = 0; j < NT; ++j) c += key >= s_key[j] ? 1 : 0;
+    return c;
+  };
+  for (int j = wave; j < NT; j += NW) {
+    const int n = s_cnt[j];
+    if (s_slot[j] != j || n > kCap) continue;
+    for (int i = lane; i < n; i += 64) add(class_of(s_cand[j][i]), key_value(s_cand[j][i]));
   }
+  if (!listed) {
+#pragma unroll
+    for (int e = 0; e < E4; ++e)
+      if (tid + e * T < nq)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const uint32_t m = s_mark[bucket(v[e][t])];
+          if (m & 0x40u) add(class_of(sort_key(v[e][t])), v[e][t]);
+        }
+  }
+  __syncthreads();
+  // the T sums of a class: LPB lanes take T / LPB each, then a butterfly
+  // (sums of the high parts without error, their errors with the low parts)
+  constexpr int LPB = T / NB < 64 ? T / NB : 64;
+  if (tid < NB * LPB) {
+    const int c = tid / LPB, l = tid % LPB;
+    double2 a = sums[c * T + l];
+#pragma unroll
+    for (int i = 1; i < T / LPB; ++i) {
+      const double2 o = sums[c * T + LPB * i + l];
+      dd_add(a.x, a.y, o.x);
+      a.y += o.y;
+    }
+#pragma unroll
+    for (int off = LPB / 2; off >= 1; off >>= 1) {
+      const double h = __shfl_xor(a.x, off, 64), o = __shfl_xor(a.y, off, 64);
+      dd_add(a.x, a.y, h);
+      a.y += o;
+    }
+    if (l == 0) {
+      s_hi[c] = a.x;
+      s_lo2[c] = a.y;
+    }
+  }
+  __syncthreads();
+  if (tid < NB) {
+    double h = s_hi[tid], l = s_lo2[tid];
+    if (tid < NT) dd_add(h, l, (double)((tid + 1) * cnt - s_less[tid]) * (double)key_value(s_key[tid]));
+    if (tid > 0) dd_add(h, l, -((double)(tid * cnt - s_less[tid - 1]) * (double)key_value(s_key[tid - 1])));
+    const uint16_t entry = f64_to_f16_rne((h + l) / (double)cnt);
+    s_entry[tid] = entry;
+    lut[row * NB + tid] = entry;
+  }
+  __syncthreads();
+
+  // ---- 4. codes
+  float mid[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+    mid[j] = f64_to_f32_down((f16_bits_to_f64(s_entry[j]) + f16_bits_to_f64(s_entry[j + 1])) * 0.5);
+  const int l0 = lane & ~7;
+#pragma unroll
+  for (int e = 0; e < E4; ++e) {
+    const int q = tid + e * T, g = q >> 3;   // q % 8 == sub: the quad's place in its group
+    uint32_t sel = 0u;
+    if (q < nq) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) sel |= code_of<NT>(v[e][t], mid) << (8 * t);
+    }
+    if constexpr (BITS == 3) {
+      const int p = l0 + 2 * min(sub, 2);
+      const uint32_t a = (uint32_t)__shfl((int)sel, p, 64), b = (uint32_t)__shfl((int)sel, p + 1, 64);
+      const uint32_t s6 = (uint32_t)__shfl((int)sel, l0 + 6, 64), s7 = (uint32_t)__shfl((int)sel, l0 + 7, 64);
+      uint32_t w = a | (b << 3);
+      w |= sub == 0 ? (s6 & 0x03030303u) << 6
+           : sub == 1 ? (s7 & 0x03030303u) << 6
+                      : ((s6 & 0x04040404u) << 4) | ((s7 & 0x04040404u) << 5);
+      if (sub < 3 && g < KC * 4) *code_dword(g) = w;
+    } else {
+      uint32_t w = sel << (2 * (sub & 3));
+      w |= (uint32_t)__shfl_xor((int)w, 1, 64);
+      w |= (uint32_t)__shfl_xor((int)w, 2, 64);
+      if ((sub & 3) == 0 && g < KC * 4) code_dword(g)[(sub >> 2) - sub] = w;
+    }
+  }
+}
+
+// Threads and float4 per thread for rows of K: as few wavefronts as hold the
+// row in registers, since the scan and the merges are per-thread work.
+template <int BITS>
+hipError_t launch_pack_rows(const float* W, int64_t N, int64_t K, const LutView& out, hipStream_t s) {
+  typedef void (*kern_t)(const float*, int64_t, int64_t, int, int, uint8_t*, uint16_t*);
+  struct Pick {
+    int64_t cols;
+    kern_t kern;
+    int threads;
+    size_t lds;
+  };
+#define DQ_PACK_ROWS(T, E4) \
+  Pick { (int64_t)T * E4 * 4, pack_lut_per_row_kernel<BITS, T, E4>, T, pack_rows_lds<BITS, T>() }
+  static const Pick picks[] = {DQ_PACK_ROWS(128, 2), DQ_PACK_ROWS(128, 4), DQ_PACK_ROWS(128, 8), DQ_PACK_ROWS(128, 10),
+                               DQ_PACK_ROWS(256, 8), DQ_PACK_ROWS(512, 6), DQ_PACK_ROWS(512, 9),
+                               DQ_PACK_ROWS(1024, 6), DQ_PACK_ROWS(1024, 8)};
+#undef DQ_PACK_ROWS
+  const Pick* p = picks;
+  while (p->cols < K) ++p;   // K <= 32768
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(p->kern),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)p->lds);
+  if (e != hipSuccess) return e;
+  const int64_t tiles = round_up(N, 16) / 16;
+  hipLaunchKernelGGL(p->kern, dim3((unsigned)(round_up(tiles, 8) * 16)), dim3(p->threads), p->lds, s, W, N, tiles,
+                     (int)K, (int)(round_up(K, 128) / 128), out.codes, out.lut);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- PAPER_GRID
@@ -326,15 +609,7 @@ hipError_t launch_pack_lut(const float* W, int64_t N, int64_t K, const uint16_t*
   const int64_t N16 = round_up(N, 16), KC = round_up(K, 128) / 128;
   if (N16 == 0) return hipSuccess;
   if (out.mode == 0) {
-    int64_t P = 64;
-    while (P < K) P <<= 1;
-    const size_t lds = (size_t)P * 4;
-    auto kern = out.bits == 3 ? pack_lut_per_row_kernel<3> : pack_lut_per_row_kernel<2>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)N16), dim3(1024), lds, s, W, N, K, P, KC, out.codes, out.lut);
-    return hipGetLastError();
+    return out.bits == 3 ? launch_pack_rows<3>(W, N, K, out, s) : launch_pack_rows<2>(W, N, K, out, s);
   }
   const int NL = 1 << out.bits;
   Grid g{};
