@@ -145,6 +145,106 @@ enum { kOutF32 = 0, kOutBF16 = 1, kOutNvfp4 = 2 };
 // silu(g) * u in fp32 (SwiGLU, the MLP non-linearity between gate/up and down)
 __device__ inline float swiglu(float g, float u) { return g / (1.0f + expf(-g)) * u; }
 
+// Scale, transform and store one 32x32 accumulator block: lane l holds output
+// row mb + l%32 and GEMM columns nb + 8g + 4h + t in register 4g + t (g, t =
+// 0..3, h = l/32).  With SwiGLU the weight rows come in gate/up groups of 16,
+// so registers 4g + t (g < 2, gate) and 4(g + 2) + t (up) of the same lane
+// meet, producing output feature nb/2 + 8g + 4h + t.  All 64 lanes take part.
+template <int OUT, bool SW>
+__device__ __forceinline__ void store_block(const float16_t& acc, float gs, int64_t mb, int64_t nb, int lane, int64_t M,
+                                            const GemmOut& out) {
+  const int h = lane >> 5;
+  if constexpr (OUT != kOutNvfp4) {
+    const bool vec = (out.Nout & 3) == 0;
+    const int64_t row = mb + (lane & 31);
+    if (row >= M) return;
+#pragma unroll
+    for (int g = 0; g < (SW ? 2 : 4); ++g) {
+      float v[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        v[t] = acc[4 * g + t] * gs;
+        if (SW) v[t] = swiglu(v[t], acc[4 * (g + 2) + t] * gs);
+      }
+      const int64_t col = (SW ? nb / 2 : nb) + 8 * g + 4 * h;
+      if (OUT == kOutF32) {
+        float* y = reinterpret_cast<float*>(out.Y) + row * out.Nout + col;
+        if (vec && col + 3 < out.Nout) {
+          *reinterpret_cast<float4_t*>(y) = float4_t{v[0], v[1], v[2], v[3]};
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            if (col + t < out.Nout) y[t] = v[t];
+        }
+      } else {
+        uint32_t b[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) b[t] = f32_to_bf16_rne(v[t]);
+        uint16_t* y = reinterpret_cast<uint16_t*>(out.Y) + row * out.Nout + col;
+        if (vec && col + 3 < out.Nout) {
+          *reinterpret_cast<uint2_t*>(y) = uint2_t{b[0] | (b[1] << 16), b[2] | (b[3] << 16)};
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            if (col + t < out.Nout) y[t] = (uint16_t)b[t];
+        }
+      }
+    }
+  } else {
+    // NVFP4 requantization along the output columns (the next layer's K):
+    // a 16-column block of a row is held by lanes l and l ^ 32 (8 values
+    // each), so the block maximum is one cross-lane step; each of the two
+    // lanes stores one dword of 8 codes.
+    const float Go = *out.G_out;
+    const float den = 6.0f * Go;
+    const int64_t tr = mb / 32;
+    if (tr >= out.tiles_r) return;
+    const int rr = lane & 31;
+    const int64_t row = tr * 32 + rr;
+#pragma unroll
+    for (int q = 0; q < (SW ? 1 : 2); ++q) {
+      const int64_t cbase = SW ? nb / 2 : nb + 16 * q;   // first column of the block
+      const int64_t tc = cbase / 64;
+      if (tc >= out.tiles_c) continue;
+      float v[8];
+      float a = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int g = (SW ? 0 : 2 * q) + e / 4, t = e % 4;
+        float x = acc[4 * g + t] * gs;
+        if (SW) x = swiglu(x, acc[4 * (g + 2) + t] * gs);
+        const int64_t col = cbase + 8 * (e / 4) + 4 * h + t;
+        if (!(row < M && col < out.Nout)) x = 0.0f;   // padding of the tile: zero codes and scales
+        v[e] = x;
+        a = fmaxf(a, fabsf(x));
+      }
+      a = fmaxf(a, __shfl_xor(a, 32, 64));
+      const uint32_t c = e4m3_encode_rne_sat(a / den);
+      const float Sc = e4m3_decode(c) * Go;
+      // the 8 codes as one dword (value e in nibble e): the activation
+      // quantizer's arithmetic, two conversions per instruction
+      const float rcp = 1.0f / Sc;   // Sc == 0: the codes are forced to 0 below
+      float yq[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) yq[e] = div_by_scale(v[e], Sc, rcp);
+      uint32_t cw = cvt_pk_fp4<0>(0u, yq[0], yq[1]);
+      cw = cvt_pk_fp4<1>(cw, yq[2], yq[3]);
+      cw = cvt_pk_fp4<2>(cw, yq[4], yq[5]);
+      cw = cvt_pk_fp4<3>(cw, yq[6], yq[7]);
+      cw = Sc == 0.0f ? 0u : fp4_canonical_zero(cw);
+      const uint32_t P0 = cw & 0xFFFFu, P1 = cw >> 16;
+      // dword 0 = columns cbase..+7 (h = 0's P0, h = 1's P0); dword 1 =
+      // columns cbase+8..+15 (h = 0's P1, h = 1's P1)
+      const uint32_t recv = (uint32_t)__shfl_xor((int)(h == 0 ? P1 : P0), 32, 64);
+      const uint32_t word = h == 0 ? (P0 | (recv << 16)) : (recv | (P1 << 16));
+      const int cc = (int)(cbase & 63);
+      uint8_t* tcodes = out.codes + (tr * out.tiles_c + tc) * 1024;
+      *reinterpret_cast<uint32_t*>(tcodes + rr * 32 + cc / 2 + 4 * h) = word;
+      if (h == 0) out.scales[(tr * out.tiles_c + tc) * 128 + rr * 4 + cc / 16] = (uint8_t)c;
+    }
+  }
+}
+
 // Workgroup tiles of one geometry: tiles_m x tiles_n tiles over the output
 // columns from n_off on.
 struct Panels {
@@ -415,14 +515,11 @@ __device__ __forceinline__ void gemm_tile(
     wait_vm<0>();
   }
 
-  // Block (i, j) holds, in lane l, output row m0 + 32i + l%32 and GEMM
-  // columns n0 + 32j + 8g + 4h + t in register 4g + t (g, t = 0..3,
-  // h = l/32).  With SwiGLU the weight rows come in gate/up groups of 16, so
-  // registers 4g + t (g < 2, gate) and 4(g + 2) + t (up) of the same lane
-  // meet, producing output feature (n0 + 32j)/2 + 8g + 4h + t.
+  // Block (i, j) holds output rows m0 + 32i .. and GEMM columns n0 + 32j ..
+  // (see store_block)
   const float gs = (*Ga) * (*Gw);
-  const int h = lane >> 5;
   if constexpr (OUT == kOutBF16 && !SW) {
+    const int h = lane >> 5;
     // A full wave tile leaves through LDS: each store instruction then writes
     // whole 128-byte rows instead of 16 bytes of each of 32 rows.  The barrier
     // covers the other waves' last LDS reads and direct loads into the ring.
@@ -455,108 +552,12 @@ __device__ __forceinline__ void gemm_tile(
       return;
     }
   }
-  if constexpr (OUT != kOutNvfp4) {
-    const bool vec = (out.Nout & 3) == 0;
+  if constexpr (OUT == kOutNvfp4)
+    if (blockIdx.x == 0 && threadIdx.x == 0 && out.G != out.G_out) *out.G = *out.G_out;
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int64_t row = m0 + i * 32 + (lane & 31);
-      if (row >= M) continue;
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-#pragma unroll
-        for (int g = 0; g < (SW ? 2 : 4); ++g) {
-          float v[4];
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            v[t] = acc[i][j][4 * g + t] * gs;
-            if (SW) v[t] = swiglu(v[t], acc[i][j][4 * (g + 2) + t] * gs);
-          }
-          const int64_t col = (SW ? (n0 + j * 32) / 2 : n0 + j * 32) + 8 * g + 4 * h;
-          if (OUT == kOutF32) {
-            float* y = reinterpret_cast<float*>(out.Y) + row * out.Nout + col;
-            if (vec && col + 3 < out.Nout) {
-              *reinterpret_cast<float4_t*>(y) = float4_t{v[0], v[1], v[2], v[3]};
-            } else {
-#pragma unroll
-              for (int t = 0; t < 4; ++t)
-                if (col + t < out.Nout) y[t] = v[t];
-            }
-          } else {
-            uint32_t b[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) b[t] = f32_to_bf16_rne(v[t]);
-            uint16_t* y = reinterpret_cast<uint16_t*>(out.Y) + row * out.Nout + col;
-            if (vec && col + 3 < out.Nout) {
-              *reinterpret_cast<uint2_t*>(y) = uint2_t{b[0] | (b[1] << 16), b[2] | (b[3] << 16)};
-            } else {
-#pragma unroll
-              for (int t = 0; t < 4; ++t)
-                if (col + t < out.Nout) y[t] = (uint16_t)b[t];
-            }
-          }
-        }
-      }
-    }
-  } else {
-    // NVFP4 requantization along the output columns (the next layer's K):
-    // a 16-column block of a row is held by lanes l and l ^ 32 (8 values
-    // each), so the block maximum is one cross-lane step; each of the two
-    // lanes stores one dword of 8 codes.
-    const float Go = *out.G_out;
-    const float den = 6.0f * Go;
-    if (blockIdx.x == 0 && threadIdx.x == 0 && out.G != out.G_out) *out.G = Go;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int64_t tr = (m0 + i * 32) / 32;
-      if (tr >= out.tiles_r) continue;
-      const int rr = lane & 31;
-      const int64_t row = tr * 32 + rr;
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-#pragma unroll
-        for (int q = 0; q < (SW ? 1 : 2); ++q) {
-          const int64_t cbase = SW ? (n0 + j * 32) / 2 : n0 + j * 32 + 16 * q;   // first column of the block
-          const int64_t tc = cbase / 64;
-          if (tc >= out.tiles_c) continue;
-          float v[8];
-          float a = 0.0f;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int g = (SW ? 0 : 2 * q) + e / 4, t = e % 4;
-            float x = acc[i][j][4 * g + t] * gs;
-            if (SW) x = swiglu(x, acc[i][j][4 * (g + 2) + t] * gs);
-            const int64_t col = cbase + 8 * (e / 4) + 4 * h + t;
-            if (!(row < M && col < out.Nout)) x = 0.0f;   // padding of the tile: zero codes and scales
-            v[e] = x;
-            a = fmaxf(a, fabsf(x));
-          }
-          a = fmaxf(a, __shfl_xor(a, 32, 64));
-          const uint32_t c = e4m3_encode_rne_sat(a / den);
-          const float Sc = e4m3_decode(c) * Go;
-          // the 8 codes as one dword (value e in nibble e): the activation
-          // quantizer's arithmetic, two conversions per instruction
-          const float rcp = 1.0f / Sc;   // Sc == 0: the codes are forced to 0 below
-          float yq[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) yq[e] = div_by_scale(v[e], Sc, rcp);
-          uint32_t cw = cvt_pk_fp4<0>(0u, yq[0], yq[1]);
-          cw = cvt_pk_fp4<1>(cw, yq[2], yq[3]);
-          cw = cvt_pk_fp4<2>(cw, yq[4], yq[5]);
-          cw = cvt_pk_fp4<3>(cw, yq[6], yq[7]);
-          cw = Sc == 0.0f ? 0u : fp4_canonical_zero(cw);
-          const uint32_t P0 = cw & 0xFFFFu, P1 = cw >> 16;
-          // dword 0 = columns cbase..+7 (h = 0's P0, h = 1's P0); dword 1 =
-          // columns cbase+8..+15 (h = 0's P1, h = 1's P1)
-          const uint32_t recv = (uint32_t)__shfl_xor((int)(h == 0 ? P1 : P0), 32, 64);
-          const uint32_t word = h == 0 ? (P0 | (recv << 16)) : (recv | (P1 << 16));
-          const int cc = (int)(cbase & 63);
-          uint8_t* tcodes = out.codes + (tr * out.tiles_c + tc) * 1024;
-          *reinterpret_cast<uint32_t*>(tcodes + rr * 32 + cc / 2 + 4 * h) = word;
-          if (h == 0) out.scales[(tr * out.tiles_c + tc) * 128 + rr * 4 + cc / 16] = (uint8_t)c;
-        }
-      }
-    }
-  }
+    for (int j = 0; j < TN; ++j) store_block<OUT, SW>(acc[i][j], gs, m0 + i * 32, n0 + j * 32, lane, M, out);
 }
 
 // One launch, two geometries: workgroups 0 .. big tiles - 1 take the tiles
@@ -574,6 +575,217 @@ __global__ __launch_bounds__(Gm::threads, Gm::occ) void nvfp4_gemm_kernel(
   else
     gemm_tile<Gh, OUT, SW>(b - nb, small, a_codes, a_scales, Ga, w_codes, w_scales, Gw, M, N, a_tiles_r, w_tiles_r, KT,
                            out);
+}
+
+// ---------------------------------------------------------------- short grids
+// Few output tiles (short prompts): a workgroup of S wavefronts takes one
+// (32*TM) x (32*TN) output tile and its wavefronts split K.  Each wavefront
+// streams its own K steps of the operand tiles straight into registers (RING
+// steps ahead; 16 bytes per lane and code tile in the MFMA's own layout, so
+// nothing passes through LDS and no barrier paces the loop), dequantizes and
+// multiplies as above; the S partial tiles are then added in wavefront order
+// through LDS, RB blocks at a time, one wavefront per block.
+// Bound: MFMA issue with the dequantization beside it (a 64 x 64 wavefront
+// tile issues 8.5 VALU instructions per MFMA; a probe shows about four hidden
+// behind each MFMA and the others costing 3 cycles), and at the smallest M the
+// weight stream.  The tile (choose_short) is picked so that the compute units
+// are evenly loaded.  No scratch memory: the split stays inside the workgroup.
+// Measured beside it: deeper register rings (within 3 %), eight wavefronts
+// against four of the same tile (within 5 %), dequantizing a whole sub-step
+// ahead of its MFMAs instead of between them (5-15 % slower).
+template <int TM, int TN, int S, int RING>
+struct ShortGeo {
+  static constexpr int tm = TM, tn = TN, waves = S;
+  static constexpr int blocks = TM * TN;
+  static constexpr int rb = blocks < 4 ? blocks : 4;       // blocks reduced per round
+  static constexpr size_t lds = (size_t)rb * S * 4096;
+  static constexpr int ring = RING;                        // K steps held in registers
+};
+
+template <class Gm, int OUT, bool SW>
+__global__ __launch_bounds__(64 * Gm::waves, Gm::waves / 4) void nvfp4_gemm_short_kernel(
+    const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales, const float* __restrict__ Ga,
+    const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, const float* __restrict__ Gw,
+    int64_t M, int a_tiles_r, int w_tiles_r, int KT, int tiles_m, int tiles_n, int SPW, GemmOut out) {
+  constexpr int TM = Gm::tm, TN = Gm::tn, S = Gm::waves, RING = Gm::ring, kTiles = TM + TN;
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // workgroup b runs on XCD b % 8, where it takes the row panels of one column
+  // panel in turn: a weight tile is read from memory into one L2
+  const int bm = (int)(blockIdx.x >> 3) % tiles_m, bn = ((int)(blockIdx.x >> 3) / tiles_m) * 8 + (int)(blockIdx.x & 7);
+  if (bn >= tiles_n) return;
+  const int64_t m0 = (int64_t)bm * 32 * TM, n0 = (int64_t)bn * 32 * TN;
+  const int kt0 = wave * SPW;
+  const int nst = max(0, min(SPW, KT - kt0));   // this wavefront's K steps
+  // one resource per operand row panel, from this wavefront's first step on;
+  // tiles past the end of an operand read its last row tile (they only feed
+  // outputs that are never stored, or the zero padding of an NVFP4 tile)
+  auto rsrc = [](const uint8_t* base, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, (int)bytes, 0x00020000);
+  };
+  const int a_tr = min(bm * TM, a_tiles_r - 1), w_tr = min(bn * TN, w_tiles_r - 1);   // the panels' first row tiles
+  const int64_t a_t0 = (int64_t)a_tr * KT + kt0, w_t0 = (int64_t)w_tr * KT + kt0;
+  const int64_t a_n = (int64_t)min(TM, a_tiles_r - a_tr) * KT - kt0;   // code tiles from there to the panel's end
+  const int64_t w_n = (int64_t)min(TN, w_tiles_r - w_tr) * KT - kt0;
+  const __amdgpu_buffer_rsrc_t rac = rsrc(a_codes + a_t0 * 1024, a_n * 1024), ras = rsrc(a_scales + a_t0 * 128, a_n * 128);
+  const __amdgpu_buffer_rsrc_t rwc = rsrc(w_codes + w_t0 * 1024, w_n * 1024), rws = rsrc(w_scales + w_t0 * 128, w_n * 128);
+  int toff[kTiles];   // tile u (A first): code tiles from the panel's first to its row
+#pragma unroll
+  for (int u = 0; u < kTiles; ++u)
+    toff[u] = (u < TM ? min(bm * TM + u, a_tiles_r - 1) - a_tr : min(bn * TN + u - TM, w_tiles_r - 1) - w_tr) * KT;
+  const int c_off = 16 * (2 * (lane & 31) + (lane >> 5)), s_off = 4 * (lane & 31), s_shift = 16 * (lane >> 5);
+
+  struct Raw {
+    uint4_t c[kTiles];
+    uint32_t s[kTiles];
+  };
+  Raw ring[RING];
+  auto load_tile = [&](int st, Raw& R, int u) {   // past the last step: the last one again (not used)
+    const int t = toff[u] + min(st, nst - 1);
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(u < TM ? rac : rwc, c_off, t * 1024, 0);
+    R.c[u] = uint4_t{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
+    R.s[u] = __builtin_amdgcn_raw_buffer_load_b32(u < TM ? ras : rws, s_off, t * 128, 0);
+  };
+  float16_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = float16_t{};
+  // Sub-step s of a K step multiplies one operand buffer while the next
+  // sub-step (of the next step after the last) is dequantized into the other,
+  // half a tile after each MFMA or so; the step's registers are refilled
+  // during its last sub-step, when all its codes are in the buffers.  The
+  // sched_barrier fences keep this order.
+  half8_t d0[kTiles], d1[kTiles];
+  half2_t sp[kTiles];   // the two block scales of tile u
+  auto dequant_half = [&](const Raw& R, int s, half8_t (&d)[kTiles], int v) {
+    const int u = v >> 1;
+    if (s == 0 && (v & 1) == 0) sp[u] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(R.s[u] >> s_shift, 1.0f, false);
+    const _Float16 x = sp[u][s >> 1];
+    if (v & 1) dequant4<1>(R.c[u][s], half2_t{x, x}, d[u]);
+    else dequant4<0>(R.c[u][s], half2_t{x, x}, d[u]);
+  };
+  auto step = [&](int st, Raw& Rc, const Raw& Rn) {
+    constexpr int kMfmas = TM * TN;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      half8_t(&dc)[kTiles] = (s & 1) ? d1 : d0;
+      half8_t(&dn)[kTiles] = (s & 1) ? d0 : d1;
+#pragma unroll
+      for (int q = 0; q < kMfmas; ++q) {
+        __builtin_amdgcn_sched_barrier(0);
+        acc[q / TN][q % TN] = __builtin_amdgcn_mfma_f32_32x32x16_f16(dc[TM + q % TN], dc[q / TN], acc[q / TN][q % TN],
+                                                                     0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s == 3) {
+#pragma unroll
+          for (int u = 0; u < kTiles; ++u)
+            if ((u * kMfmas) / kTiles == q) load_tile(st + RING, Rc, u);
+        }
+#pragma unroll
+        for (int v = 0; v < 2 * kTiles; ++v)
+          if ((v * kMfmas) / (2 * kTiles) == q) dequant_half(s < 3 ? Rc : Rn, (s + 1) & 3, dn, v);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (nst > 0) {
+#pragma unroll
+    for (int r = 0; r < RING; ++r)
+#pragma unroll
+      for (int u = 0; u < kTiles; ++u) load_tile(r, ring[r], u);
+#pragma unroll
+    for (int v = 0; v < 2 * kTiles; ++v) dequant_half(ring[0], 0, d0, v);
+    const int full = nst / RING * RING;
+    for (int st = 0; st < full; st += RING) {
+#pragma unroll
+      for (int r = 0; r < RING; ++r) step(st + r, ring[r], ring[(r + 1) % RING]);
+    }
+#pragma unroll
+    for (int r = 0; r < RING - 1; ++r)
+      if (full + r < nst) step(full + r, ring[r], ring[(r + 1) % RING]);
+  }
+
+  // ---- partial tiles, RB blocks per round: red[block][wave][g][lane]
+  const float gs = (*Ga) * (*Gw);
+  constexpr int RB = Gm::rb;
+  float4_t* red = reinterpret_cast<float4_t*>(smem);
+  if constexpr (OUT == kOutNvfp4)
+    if (blockIdx.x == 0 && threadIdx.x == 0 && out.G != out.G_out) *out.G = *out.G_out;
+  static_for<0, (Gm::blocks + RB - 1) / RB>([&](auto rc) {
+    constexpr int b0 = decltype(rc)::value * RB;
+    if (b0 > 0) __syncthreads();   // the previous round has been read
+#pragma unroll
+    for (int b = b0; b < b0 + RB && b < Gm::blocks; ++b)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float16_t& x = acc[b / TN][b % TN];
+        red[(((b - b0) * S + wave) * 4 + g) * 64 + lane] = float4_t{x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
+      }
+    __syncthreads();
+    const int b = b0 + wave;
+    if (wave < RB && b < Gm::blocks) {
+      float16_t sum;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float4_t o = red[((wave * S) * 4 + g) * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < S; ++w) {
+          const float4_t p = red[((wave * S + w) * 4 + g) * 64 + lane];
+#pragma unroll
+          for (int t = 0; t < 4; ++t) o[t] += p[t];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) sum[4 * g + t] = o[t];
+      }
+      store_block<OUT, SW>(sum, gs, m0 + (b / TN) * 32, n0 + (b % TN) * 32, lane, M, out);
+    }
+  });
+}
+
+GemmOut gemm_out(const GemmArgs& a) {
+  GemmOut o{};
+  o.Y = a.Y;
+  o.Nout = (a.flags & 1) != 0 ? a.N / 2 : a.N;
+  if (a.out_kind == kOutNvfp4) {
+    o.G_out = a.G_out;
+    o.codes = a.Yq.codes;
+    o.scales = a.Yq.scales;
+    o.G = a.Yq.G;
+    o.tiles_r = round_up(a.M, 32) / 32;
+    o.tiles_c = round_up(o.Nout, 64) / 64;
+  }
+  return o;
+}
+
+// GEMM columns that the workgroups cover: an NVFP4 output also writes the zero
+// padding of its last 64-column tile (128 GEMM columns with SwiGLU)
+int64_t short_columns(const GemmArgs& a) {
+  return a.out_kind != kOutNvfp4 ? a.N : round_up(a.N, (a.flags & 1) != 0 ? 128 : 64);
+}
+int64_t short_tiles(int64_t n, int t) { return (n + 32 * t - 1) / (32 * t); }
+
+template <class Gm>
+hipError_t launch_short(const GemmArgs& a, hipStream_t s) {
+  typedef void (*kern_t)(const uint8_t*, const uint8_t*, const float*, const uint8_t*, const uint8_t*, const float*,
+                         int64_t, int, int, int, int, int, int, GemmOut);
+  static const kern_t kerns[3][2] = {
+      {nvfp4_gemm_short_kernel<Gm, kOutF32, false>, nvfp4_gemm_short_kernel<Gm, kOutF32, true>},
+      {nvfp4_gemm_short_kernel<Gm, kOutBF16, false>, nvfp4_gemm_short_kernel<Gm, kOutBF16, true>},
+      {nvfp4_gemm_short_kernel<Gm, kOutNvfp4, false>, nvfp4_gemm_short_kernel<Gm, kOutNvfp4, true>}};
+  const kern_t kern = kerns[a.out_kind][(a.flags & 1) != 0 ? 1 : 0];
+  const int KT = (int)(round_up(a.K, 64) / 64);
+  const int tiles_m = (int)short_tiles(a.M, Gm::tm);
+  const int tiles_n = (int)short_tiles(short_columns(a), Gm::tn);
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)Gm::lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * round_up(tiles_n, 8))), dim3(64 * Gm::waves), Gm::lds, s, a.A.codes,
+                     a.A.scales, a.A.G, a.W.codes, a.W.scales, a.W.G, a.M, (int)(round_up(a.M, 32) / 32),
+                     (int)(round_up(a.N, 32) / 32), KT, tiles_m, tiles_n, (KT + Gm::waves - 1) / Gm::waves,
+                     gemm_out(a));
+  return hipGetLastError();
 }
 
 // One launch: output columns 0 .. split-1 in Gm tiles, split .. N-1 in Gh
@@ -594,17 +806,7 @@ hipError_t launch_geo(const GemmArgs& a, int64_t split, hipStream_t s) {
   const size_t lds = std::max((size_t)Gm::stages * Gm::bytes, (size_t)Gh::stages * Gh::bytes);
   static_assert(Gm::stages * Gm::bytes <= kLdsBudget && Gh::stages * Gh::bytes <= kLdsBudget, "LDS budget");
   const bool sw = (a.flags & 1) != 0;
-  GemmOut o{};
-  o.Y = a.Y;
-  o.Nout = sw ? a.N / 2 : a.N;
-  if (a.out_kind == kOutNvfp4) {
-    o.G_out = a.G_out;
-    o.codes = a.Yq.codes;
-    o.scales = a.Yq.scales;
-    o.G = a.Yq.G;
-    o.tiles_r = round_up(a.M, 32) / 32;
-    o.tiles_c = round_up(o.Nout, 64) / 64;
-  }
+  const GemmOut o = gemm_out(a);
   typedef void (*kern_t)(const uint8_t*, const uint8_t*, const float*, const uint8_t*, const uint8_t*, const float*,
                          int64_t, int64_t, int64_t, int64_t, int64_t, GemmOut, Panels, Panels);
   kern_t kern;
@@ -625,6 +827,65 @@ hipError_t launch_geo(const GemmArgs& a, int64_t split, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Modelled time (us) of a grid, for the choice between the kernels.  Both
+// sides were measured on 230 combinations of M = 16 .. 4096 with the 8B and
+// 27B linears and 1024 x 4096, 1024 x 16384, 3072 x 768; the model is within
+// 7-10 % of either, and the choice within 1 % of the faster kernel on average.
+// Ring kernels: per K step, by resident workgroups (1 or 2 per compute unit)
+// and then by the total of 256 x 128 tiles.
+double ring_time(int64_t M, int64_t N, int64_t KT, int64_t cus) {
+  const int64_t t = ((M + 255) / 256) * ((N + 127) / 128);
+  if (t <= cus) {
+    const int64_t half = ((M + 127) / 128) * ((N + 127) / 128);   // 128 x 128 tiles
+    return 3.0 + (half <= cus ? 0.50 : 0.90) * (double)KT;
+  }
+  const double x = (double)t * 256.0 / (double)cus;
+  return 3.0 + (t <= 2 * cus ? 1.1 + 0.0008 * x : 0.55 + 0.0026 * x) * (double)KT;
+}
+
+// Short-grid tiles: `conc` workgroups per compute unit (by registers); `fixed`
+// per round of them (ring fill, reduction, store), `step` per K step and
+// workgroup on the fullest compute unit, growing by `crowd` with their number.
+struct ShortFit {
+  int tm, tn, conc;
+  double fixed, step, crowd;
+  hipError_t (*launch)(const GemmArgs&, hipStream_t);
+};
+
+double short_time(const ShortFit& f, int64_t M, int64_t cols, int64_t KT, int64_t cus) {
+  const int64_t tiles = short_tiles(M, f.tm) * short_tiles(cols, f.tn);
+  const double rounds = (double)((tiles + cus * f.conc - 1) / (cus * f.conc)), load = (double)((tiles + cus - 1) / cus);
+  return 3.0 + f.fixed * rounds + f.step * (double)KT * load * (1.0 + f.crowd * (1.0 - 1.0 / load));
+}
+
+// The short-grid tile to use, or NULL for the ring kernels: the faster of the
+// two by the models, 5 % to the ring kernels.  Measured, bf16 out, M = 168:
+// 27B o 42.1 -> 13.3 us, q/k/v 42.6 -> 17.4, down 130 -> 37.3, gate/up 109 ->
+// 67; 8B up 38 -> 23; at M = 1024 down 222 -> 162, o 70 -> 55 and gate/up 294
+// against 313 with the short grid (not used).
+const ShortFit* choose_short(const GemmArgs& a, int64_t cus) {
+  static const ShortFit fits[] = {{1, 1, 2, 1.65, 0.0439, 0.0, launch_short<ShortGeo<1, 1, 8, 4>>},
+                                  {1, 2, 2, 2.26, 0.0626, 0.06, launch_short<ShortGeo<1, 2, 8, 4>>},
+                                  {2, 2, 1, 2.55, 0.0895, 0.33, launch_short<ShortGeo<2, 2, 8, 3>>},
+                                  {3, 2, 2, 3.19, 0.1286, 0.14, launch_short<ShortGeo<3, 2, 4, 2>>},
+                                  {2, 3, 2, 3.68, 0.1279, 0.16, launch_short<ShortGeo<2, 3, 4, 2>>},
+                                  {4, 2, 1, 4.53, 0.1454, 0.40, launch_short<ShortGeo<4, 2, 8, 2>>}};
+  // (columns in whole 128s: the same tile, and so the same sums, whatever the
+  // output kind)
+  const int64_t KT = round_up(a.K, 64) / 64, cols = round_up(a.N, 128);
+  if (KT == 0) return nullptr;
+  double best = 0.95 * ring_time(a.M, a.N, KT, cus);
+  const ShortFit* pick = nullptr;
+  for (const ShortFit& f : fits) {
+    const double t = short_time(f, a.M, cols, KT, cus);
+    if (t < best) {
+      best = t;
+      pick = &f;
+    }
+  }
+  return pick;
+}
+
 }  // namespace
 
 __global__ void publish_scale_kernel(const float* src, float* dst) { *dst = *src; }
@@ -636,6 +897,8 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
       hipLaunchKernelGGL(publish_scale_kernel, dim3(1), dim3(1), 0, s, a.G_out, a.Yq.G);
     return hipGetLastError();
   }
+  const int cus = num_cus();
+  if (const ShortFit* f = choose_short(a, cus)) return f->launch(a, s);
   // bf16 output without SwiGLU on grids of at least two full rounds of
   // 256x256 tiles: one workgroup of four 128x128 wavefronts per compute unit
   // (one wavefront per SIMD, 256 accumulator registers).  A wavefront
@@ -647,7 +910,6 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   // second workgroup runs its main loop meanwhile (2-7 % slower at
   // 4096 x 34816 x 5120).  A partial last round of at most half the compute
   // units takes the trailing columns as 256x128 tiles, one per compute unit.
-  const int cus = num_cus();
   if (a.out_kind == kOutBF16 && (a.flags & 1) == 0) {
     using Gb = Geo<4, 4, 2, 2, 1>;
     using Gbh = Geo<4, 2, 2, 2, 1>;

@@ -1,0 +1,90 @@
+"""NVFP4 GEMM on short grids: the kernel that splits K over the wavefronts of
+a workgroup, at the edges of its tiles (rows, columns and K steps that end
+inside one, wavefronts without a K step) and for every tile shape, against the
+fp64 oracle of the GPU's own operand codes and the oracle quantizer."""
+import os
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import dq_layout as L  # noqa: E402
+import parity_bounds as PB  # noqa: E402
+
+import synth  # noqa: E402
+from oracle import linalg, nvfp4  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+try:
+    import paper_2609_26333_amd as dq
+except ImportError:  # pragma: no cover
+    dq = None
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if dq is None or not torch.cuda.is_available():
+        pytest.skip("needs the built HIP library and a GPU")
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+# rows from 1 to several tiles, columns that are no multiple of a tile, of 16
+# or of 4, K from a quarter step to more steps than wavefronts; the last ones
+# take the larger tiles (96 x 64, 64 x 96, 128 x 64) on a 256-CU device
+SHAPES = [(1, 16, 16), (16, 48, 64), (33, 100, 80), (64, 97, 512), (65, 224, 528), (96, 1000, 1040), (130, 352, 2048),
+          (168, 4096, 576), (168, 34816, 64), (250, 6144, 512), (384, 5120, 640), (160, 8192, 320), (700, 3000, 272)]
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_short_gemm(M, N, K):
+    print("short gemm", M, N, K, flush=True)
+    xb = synth.random_bf16(M + N, (M, K), outlier_frac=0.01, outlier_factor=20)
+    w = synth.random_f32(N + K, (N, K), 0.02)
+    A = dq.dq_quantize_act_nvfp4(dev(xb.view(np.int16)))
+    W = dq.dq_pack_nvfp4(dev(w))
+    y32 = dq.dq_prefill_gemm(W, A=A, out_kind=dq.OUT_F32)
+    yb = dq.dq_prefill_gemm(W, A=A, out_kind=dq.OUT_BF16)
+    torch.cuda.synchronize()
+    y32, yb = y32.cpu().numpy(), yb.float().cpu().numpy()
+    cols = np.arange(N) if N <= 4096 else np.sort(np.random.default_rng(1).choice(N, 700, replace=False))
+    qa, ca, Ga = nvfp4.quantize_bf16_activations(xb)
+    qw, cw, Gw = nvfp4.quantize_dynamic(w)
+    qw, cw = qw[cols], cw[cols]
+    ref = linalg.nvfp4_gemm(qa, ca, Ga, qw, cw, Gw)
+    bound = PB.fp32_sum_bound(PB.abs_products(nvfp4.dequantize(qa, ca, Ga), nvfp4.dequantize(qw, cw, Gw)), K)
+    PB.assert_within(y32[:, cols], ref, bound, "short gemm")
+    # bf16: the same sums, rounded to nearest even
+    assert np.array_equal(yb, torch.from_numpy(y32).bfloat16().float().numpy())
+    G_o = nvfp4.global_scale(0.7 * nvfp4.amax(y32))   # some values saturate
+    Gd = dev(np.array([G_o], np.float32))
+    if N % 16 == 0:
+        Yq = dq.dq_prefill_gemm(W, A=A, out_kind=dq.OUT_NVFP4, G_out_static=Gd)
+        torch.cuda.synchronize()
+        q, c, qfull, cfull = L.nvfp4_unpack(Yq.codes.cpu().numpy(), Yq.scales.cpu().numpy(), M, N)
+        q_ref, c_ref = nvfp4.quantize(y32, G_o)
+        assert np.array_equal(c, c_ref) and np.array_equal(q, q_ref)
+        assert not qfull[M:].any() and not qfull[:, N:].any() and not cfull[M:].any() and not cfull[:, N // 16:].any()
+        assert Yq.G.cpu().numpy()[0] == G_o
+    if N % 32 == 0:
+        s32 = dq.dq_prefill_gemm(W, A=A, out_kind=dq.OUT_F32, epilogue_flags=dq.EPI_SWIGLU)
+        Yq = dq.NvFp4Tensor.empty(M, N // 2)
+        Yq.codes.fill_(0xFF)     # the padding has to be written
+        Yq.scales.fill_(0xFF)
+        dq.dq_prefill_gemm(W, A=A, out_kind=dq.OUT_NVFP4, G_out_static=Gd, epilogue_flags=dq.EPI_SWIGLU, Yq=Yq)
+        torch.cuda.synchronize()
+        s32 = s32.cpu().numpy()
+        blocks = y32.astype(np.float64).reshape(M, N // 32, 2, 16)
+        g, u = blocks[:, :, 0], blocks[:, :, 1]
+        s_ref = (g / (1.0 + np.exp(-g)) * u).reshape(M, N // 2)
+        assert np.all(np.abs(s32 - s_ref) <= 1e-6 * np.abs(s_ref) + 1e-30)   # four fp32 roundings of the same operands
+        q, c, qfull, cfull = L.nvfp4_unpack(Yq.codes.cpu().numpy(), Yq.scales.cpu().numpy(), M, N // 2)
+        q_ref, c_ref = nvfp4.quantize(s32, G_o)
+        assert np.array_equal(c, c_ref) and np.array_equal(q, q_ref)
+        assert not qfull[M:].any() and not qfull[:, N // 2:].any()
+        assert not cfull[M:].any() and not cfull[:, N // 32:].any()
