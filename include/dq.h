@@ -313,13 +313,13 @@ dq_status dq_prefill_gemm_mxfp4(const dq_mxfp4_t* A, const dq_mxfp4_t* W, int ou
  * x: device bf16 [B, K] row-major, 1 <= B <= 16.  W: packed LUT weight.
  * out_kind DQ_OUT_F32 / DQ_OUT_BF16: y is device [B, N] row-major.
  * workspace: device memory of at least dq_decode_gemv_workspace_size() bytes
- *   (16-byte aligned), used for split-K partial sums when B >= 2; it must not
+ *   (16-byte aligned), room for split-K partial sums when B >= 2; it must not
  *   be in use by other work while the call runs on `stream`.  NULL: the
  *   library takes it from its own pool, stream-ordered (costs ~10 us of host
  *   time per call).  workspace_bytes below the required size is rejected.
  * Activations are converted to fp16 inside the kernel after a power-of-two
  * rescale from the largest magnitude of the slice of x that one wavefront
- * (B = 1) or one K group of a batch row (B >= 2) reads; a bf16 value is
+ * reads (B >= 2: of each batch row); a bf16 value is
  * converted exactly unless it lies more than 2^31 below that magnitude (it
  * then becomes an fp16 subnormal, truncated toward zero: an error below 2^-38
  * of the magnitude).  Products with the fp16 table are exact; partial sums

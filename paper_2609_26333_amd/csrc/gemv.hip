@@ -17,12 +17,13 @@
 //    pairs: about 1.6 VALU instructions per 3-bit weight;
 //  * the multiply-accumulate runs on MFMA (v_mfma_f32_16x16x32_f16: 16 weight
 //    rows x 32 k x 16 batch columns), so batch 1..16 costs the same VALU work;
-//  * activations are staged into LDS as fp16, rescaled by a power of two
+//  * activations are converted to fp16, rescaled by a power of two
 //    (exact products with the fp16 table); the wavefronts of a workgroup
 //    split K and reduce through LDS in a fixed order, so results are
 //    deterministic.
-// Two kernels: a persistent one (resident workgroups looping over row tiles,
-// whenever the activations fit in LDS) and a piecewise one for larger B*K.
+// Three kernels: batch 1 (resident workgroups looping over row tiles, the
+// activations in LDS), batch >= 2 (the activations in registers), and a
+// piecewise one for activations too long for either.
 #include <algorithm>
 #include <atomic>
 #include <cstdint>
@@ -166,6 +167,8 @@ __device__ i32x2_t raw_buffer_load_b64(i32x4_t rsrc, int32_t voff, int32_t soff,
                                        int32_t aux) __asm("llvm.amdgcn.raw.buffer.load.v2i32");
 __device__ i32x3_t raw_buffer_load_b96(i32x4_t rsrc, int32_t voff, int32_t soff,
                                        int32_t aux) __asm("llvm.amdgcn.raw.buffer.load.v3i32");
+__device__ i32x4_t raw_buffer_load_b128(i32x4_t rsrc, int32_t voff, int32_t soff,
+                                        int32_t aux) __asm("llvm.amdgcn.raw.buffer.load.v4i32");
 __device__ int16_t raw_buffer_load_b16(i32x4_t rsrc, int32_t voff, int32_t soff,
                                        int32_t aux) __asm("llvm.amdgcn.raw.buffer.load.i16");
 __device__ int32_t raw_buffer_load_b32(i32x4_t rsrc, int32_t voff, int32_t soff,
@@ -660,288 +663,267 @@ void lut_gemv_persist_kernel(const uint16_t* __restrict__ x, int B, int64_t K, c
 constexpr int kRingMulti = 8;
 
 // ---------------------------------------------------------------- batched
-// Batch B >= 2.  Each workgroup takes K group kg (KCR chunks) of a group of
-// W * TPW row tiles.  It copies the bf16 slice of x (all B rows) into LDS,
-// one wavefront per batch row rescales the row's slice by a power of two
-// from the slice's own maximum and converts it to fp16 in place (exact for
-// every value within 2^31 of that maximum), and each wavefront then owns TPW
-// whole tiles over the K group: its code stream is contiguous per tile and
-// it reduces nothing with other wavefronts.  The tile sums are unscaled per
-// batch row.  With one K group they are y; otherwise they go to a per-K-group
-// partial buffer that a reduction pass adds up in K-group order (results are
-// deterministic).  A hand-off between workgroups inside the kernel would
-// need a device-scope release per workgroup, which on this architecture
-// writes back the XCD's whole L2.
-struct SplitPlan {
-  int KG, TPW, KCR;   // K groups, tiles per wavefront, chunks per K group
+// Batch B >= 2: the activations live in registers.  A workgroup of up to
+// sixteen wavefronts (one workgroup of sixteen per compute unit) takes K group
+// kg (KCR chunks; one group up to 6144 columns) of a run of row tiles; its
+// wavefront w owns chunks w, w + W, .. (at most CPW) of the group for the
+// whole run (or one pass over it) and holds their activations as MFMA operands: lane (q, j) has
+// columns 32q .. 32q + 31 of batch row j of each chunk, 16 registers a chunk,
+// loaded straight from x, rescaled by a power of two from the largest
+// magnitude of the lane's row in the wavefront's chunks (exact for every value
+// within 2^31 of it) and converted to fp16 in place.  Nothing is staged in LDS
+// and nothing is shared before the reduction.  The code stream runs kAhead
+// tiles ahead.  Each wavefront parks its unscaled 16 x 16 partial tile in LDS;
+// after one barrier per kPark tiles, wavefront r adds the W partials of tile r
+// in wavefront order and stores the tile (to y, or with more than one K group
+// to the partial sums that a second pass adds in K-group order): results are
+// deterministic.
+// Bound: VALU issue of the lookups (about 54 instructions per 2048-code chunk)
+// with the code stream beside it, and at the small matrices the launch, one
+// memory round trip and the conversion (350 instructions a wavefront at three
+// chunks and batch 16, about 2 us), which every compute unit does for all of
+// x.  Against the kernel before it (K groups staged in LDS by every workgroup,
+// two barriers, a reduction launch for each matrix): 27B block, LUT3, batch 2
+// 60.8 -> 46.1 us, 8 66.6 -> 51.5, 16 70.9 -> 59.8; LUT2 with block scales at
+// batch 8 70.7 -> 55.5; 12288 x 4096 at batch 4 11.4 -> 8.3.
+struct BatchPlan {
+  int KG, KCR, TPG;   // K groups, chunks per K group, tiles per workgroup
   int tiles, KC;
 };
+typedef uint16_t ushort2_t __attribute__((ext_vector_type(2)));
+constexpr int kAhead = 2;   // tiles of codes in flight per wavefront
+constexpr int kParkBytes = 144 * 1024;
 
-template <int BITS, int MODE, int RING, int TI>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6)))
-void lut_gemv_split_kernel(const uint16_t* __restrict__ x, int64_t K, int B, const uint8_t* __restrict__ codes, const uint16_t* __restrict__ lut,
-                           const uint8_t* __restrict__ scales, const float* __restrict__ Gp, int64_t N,
-                           SplitPlan plan, float* __restrict__ partials, int out_kind, void* __restrict__ y) {
-  __builtin_amdgcn_s_setprio(3);
+// dword of the lane n places further on in its row of 16 (cyclically)
+template <int n>
+__device__ inline uint32_t row_rotate(uint32_t v) {
+  if constexpr (n == 0) return v;
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x120 + (16 - n), 0xF, 0xF, false);   // row_ror
+}
+
+// BV: batch columns (16, 8 or 4 >= B).  With fewer than 16, lanes j, j + BV,
+// .. of a row of 16 each load and convert a part of batch row j % BV's
+// columns, and exchange them by row rotations.
+template <int BITS, int MODE, int CPW, int BV>
+__global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
+    const uint16_t* __restrict__ x, int64_t K, int B, const uint8_t* __restrict__ codes,
+    const uint16_t* __restrict__ lut, const uint8_t* __restrict__ scales, const float* __restrict__ Gp, int64_t N,
+    BatchPlan plan, int park, float* __restrict__ partials, int out_kind, void* __restrict__ y) {
   typedef typename CodeVec<BITS>::type cvec;
   constexpr int kChunkBytes = 64 * CodeVec<BITS>::bytes;
   constexpr int kTabBytes = 16 * 2 * (1 << BITS);
   extern __shared__ __align__(16) uint8_t smem[];
+  float4_t* part = reinterpret_cast<float4_t*>(smem);   // [park][W][64]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int W = blockDim.x >> 6;
-  const int KG = plan.KG, TPW = plan.TPW, KCR = plan.KCR, KC = plan.KC, T = plan.tiles;
+  const int KG = plan.KG, KC = plan.KC, T = plan.tiles;
   const int kg = (int)blockIdx.x % KG, tg = (int)blockIdx.x / KG;
-  const int tw = (tg * W + wave) * TPW;                    // this wavefront's first tile
-  const int ntw = max(0, min(TPW, T - tw));                 // and its tile count
-  const int c0 = kg * KCR, nc = min(KCR, KC - c0);         // the K group's chunks
-  const int rowstride = nc * 128 + 8;                       // fp16 per staged batch row (pad staggers banks)
-  // LDS: activations [B][rowstride] | tables [W][TI KiB]; static: unscale
-  // factors and grid, copied by wavefront 0.  Tile sums go straight from the
-  // accumulators to y or to the K group's partials, so LDS holds only what
-  // the streaming reads and more workgroups fit on a compute unit.
-  __shared__ __align__(16) uint32_t s_small[32];
-  _Float16* xs = reinterpret_cast<_Float16*>(smem);
-  uint8_t* tabs = smem + round_up((int64_t)B * rowstride * 2, 16) + (size_t)wave * TI * 1024;
+  const int t0 = tg * plan.TPG, nt = min(plan.TPG, T - t0);     // this workgroup's tiles
+  const int c0 = kg * plan.KCR, nc = min(plan.KCR, KC - c0);    // and chunks
   const int i = lane & 15, j = lane & 15, q = lane >> 4;
   const bool xlane = j < B;
+  constexpr int NV = BV / 4;      // 16-byte loads per lane and chunk
+  const int jx = j % BV;          // the batch row this lane loads for
+  constexpr int32_t kNowhere = 0x7FFFFFFF;   // an offset past every buffer: the load returns zero and reads nothing
 
-  // ---- 1. the K group's slice of the raw bf16 activations, four chunks of
-  // a row per 16-byte-per-lane copy (spread over the wavefronts; lanes past
-  // the slice row stay idle, reads past K are clamped in bounds and zeroed at
-  // conversion) and this wavefront's tables
-  {
-    const int nq = (nc + 3) / 4;
-    for (int t = wave; t < B * nq; t += W) {
-      const int b = t / nq, u = 4 * (t - b * nq);
-      const int64_t k = min((int64_t)(c0 + u) * 128 + 8 * lane, K - 8);   // K % 32 == 0
-      if (lane < (nc - u) * 16)
-        __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(x + (int64_t)b * K + k),
-                                         reinterpret_cast<void*>(xs + b * rowstride + u * 128), 16, 0, 0);
-    }
-  }
-  if (MODE == 0) {   // tables of tiles tw .. tw + TPW - 1 (contiguous); reads past the array return zero
-    const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(lut), 0, (int)((int64_t)T * kTabBytes), 0x00020000);
-#pragma unroll
-    for (int ti = 0; ti < TI; ++ti)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, (__attribute__((address_space(3))) void*)(tabs + ti * 1024), 16,
-                                               lane * 16 + tw * kTabBytes + ti * 1024, 0, 0, 0);
-  }
-  // the grid into LDS as well: with only the ring's loads tracked by the
-  // compiler, its waits in the loop stay exact
-  if (MODE == 1 && wave == 0 && lane < (1 << BITS) / 2)
-    __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(lut + 2 * lane),
-                                     reinterpret_cast<void*>(s_small + 16), 4, 0, 0);
-
-  // ---- 2. the code ring: slot (tile i, chunk u) -> chunk c0 + u of tile tw + i;
-  // past the last slot the cursor stays on it
+  const i32x4_t rx = buffer_resource(x, (uint32_t)((int64_t)B * K * 2));
+  // ---- 2. tables and codes of the first tiles (past the last tile, and past
+  // the wavefront's last chunk: nothing is read)
   const i32x4_t rcodes = buffer_resource(codes, (uint32_t)T * (uint32_t)KC * kChunkBytes);
+  const i32x4_t rtab = buffer_resource(lut, (uint32_t)(T * kTabBytes));   // PER_ROW
   i32x4_t rscales{};
   if (MODE == 1) rscales = buffer_resource(scales, (uint32_t)T * (uint32_t)KC * 128);
-  const int32_t lane_code = lane * CodeVec<BITS>::bytes, lane_scale = lane * 2;
-  cvec ring[RING];
-  uint32_t sring[RING];
-  const int last = max(ntw, 1) - 1;   // a wavefront without tiles re-reads tile tw's range: in bounds
-  const int twc = min(tw, T - 1);
-  int li = 0, lu = 0;
-  auto load_next = [&](int slot) {
-    const int cidx = (twc + min(li, last)) * KC + c0 + lu;
+  const int32_t lane_code = lane * CodeVec<BITS>::bytes, lane_scale = lane * 2, lane_tab = i * 2 * (1 << BITS);
+  cvec ring[kAhead][CPW];
+  uint32_t sring[kAhead][CPW];
+  uint4_t tab[kAhead];
+  int cp = c0, nu = 0;   // this pass: first chunk, chunks of this wavefront (<= CPW)
+  auto load_chunk = [&](int t, int r, int u) {
+    const bool ok = t < nt && u < nu;
+    const int cidx = (t0 + t) * KC + cp + u * W + wave;   // (out of range: not read, whatever it is)
+    const int32_t vc = ok ? lane_code : kNowhere - 64;
     if constexpr (BITS == 3) {
-      const i32x3_t v = raw_buffer_load_b96(rcodes, lane_code, cidx * kChunkBytes, 0);
-      ring[slot] = cvec{{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2]}};
+      const i32x3_t v = raw_buffer_load_b96(rcodes, vc, cidx * kChunkBytes, 0);
+      ring[r][u] = cvec{{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2]}};
     } else {
-      const i32x2_t v = raw_buffer_load_b64(rcodes, lane_code, cidx * kChunkBytes, 0);
-      ring[slot] = cvec{{(uint32_t)v[0], (uint32_t)v[1]}};
+      const i32x2_t v = raw_buffer_load_b64(rcodes, vc, cidx * kChunkBytes, 0);
+      ring[r][u] = cvec{{(uint32_t)v[0], (uint32_t)v[1]}};
     }
-    if (MODE == 1) sring[slot] = (uint16_t)raw_buffer_load_b16(rscales, lane_scale, cidx * 128, 0);
-    if (++lu == nc) {
-      lu = 0;
-      ++li;
-    }
-    if (li == ntw) {
-      li = max(ntw, 1) - 1;
-      lu = nc - 1;
+    if (MODE == 1)
+      sring[r][u] = (uint32_t)raw_buffer_load_b32(rscales, ok ? lane_scale & ~3 : kNowhere - 64, cidx * 128, 0);
+  };
+  auto load_tab = [&](int t, int r) {
+    if constexpr (MODE == 1) return;
+    const int32_t off = t < nt ? (t0 + t) * kTabBytes + lane_tab : kNowhere - 64;
+    if constexpr (BITS == 3) {
+      const i32x4_t v = raw_buffer_load_b128(rtab, off, 0, 0);
+      tab[r] = uint4_t{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
+    } else {
+      const i32x2_t v = raw_buffer_load_b64(rtab, off, 0, 0);
+      tab[r] = uint4_t{(uint32_t)v[0], (uint32_t)v[1], 0u, 0u};
     }
   };
-  __builtin_amdgcn_sched_barrier(0);
+  uint4_t xr[CPW][4];
+  float unscale = 1.0f;
+  // ---- 3. a pass's activations (64 bytes per lane and chunk), with the codes
+  // of its first tiles behind them; rescaled and converted (see the batch-1
+  // kernel: exact, or an fp16 subnormal more than 2^31 below the maximum)
+  auto load_pass = [&]() __attribute__((always_inline)) {
 #pragma unroll
-  for (int r = 0; r < RING; ++r) load_next(r);
-  __builtin_amdgcn_sched_barrier(0);
-  // the slice and table copies were issued before the ring: wait for them
-  // (the compiler does not track loads into LDS), then make every
-  // wavefront's part of the slice visible (LDS-only barrier)
-  {
-    constexpr int kv = RING * (MODE == 1 ? 2 : 1);
-    __builtin_amdgcn_s_waitcnt((kv & 0xF) | ((kv >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-  }
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  // ---- 2b. per batch row, the slice's maximum, then fp16 in place; the
-  // row's unscale factor into LDS.  A row takes one wavefront (B <= W) or
-  // half of one (B > W: rows wave and wave + W side by side), its lanes
-  // striding over the row's dwords with eight reads in flight per round trip
-  auto to_h2 = [](uint32_t v, float sc) {
-    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(bf16_lo(v) * sc, bf16_hi(v) * sc));
-  };
-  {
-    const bool half = B > W;
-    const int tpr = half ? 32 : 64;                        // lanes per row
-    const int lr = half ? (lane & 31) : lane;
-    const int b = wave + (half ? W * (lane >> 5) : 0);
-    const bool live = b < B;                                // rows past B: reads only, of row 0
-    uint32_t* row = reinterpret_cast<uint32_t*>(xs + (live ? b : 0) * rowstride);
-    const int nd = nc * 64;   // dwords of the slice row
-    float m = 0.0f;
-    for (int d0 = lr; d0 < nd; d0 += 8 * tpr) {
-      uint32_t v[8];
+    for (int u = 0; u < CPW; ++u) {
+      const int64_t k = (int64_t)(cp + u * W + wave) * 128 + 32 * q;   // K % 32 == 0: all 32 columns inside, or none
+      const int32_t off = u < nu && jx < B && k < K ? (int32_t)((jx * K + k) * 2) + j / BV * (NV * 16) : kNowhere - 64;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = d0 + u * tpr < nd ? row[d0 + u * tpr] : 0u;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) m = fmaxf(m, fmaxf(fabsf(bf16_lo(v[u])), fabsf(bf16_hi(v[u]))));
+      for (int v = 0; v < NV; ++v) {
+        const i32x4_t w = raw_buffer_load_b128(rx, off + 16 * v, 0, 0);
+        xr[u][v] = uint4_t{(uint32_t)w[0], (uint32_t)w[1], (uint32_t)w[2], (uint32_t)w[3]};
+      }
     }
-    m = fmaxf(m, __shfl_xor(m, 1, 64));
-    m = fmaxf(m, __shfl_xor(m, 2, 64));
-    m = fmaxf(m, __shfl_xor(m, 4, 64));
-    m = fmaxf(m, __shfl_xor(m, 8, 64));
+#pragma unroll
+    for (int r = 0; r < kAhead; ++r) {
+      load_tab(r, r);
+#pragma unroll
+      for (int u = 0; u < CPW; ++u) load_chunk(r, r, u);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    ushort2_t mp{0, 0};   // magnitudes as 16-bit integers, two at a time
+#pragma unroll
+    for (int u = 0; u < CPW; ++u)
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+          mp = __builtin_elementwise_max(mp, __builtin_bit_cast(ushort2_t, xr[u][v][d] & 0x7FFF7FFFu));
+    float m = __uint_as_float((uint32_t)max(mp[0], mp[1]) << 16);
     m = fmaxf(m, __shfl_xor(m, 16, 64));
-    if (!half) m = fmaxf(m, __shfl_xor(m, 32, 64));
+    m = fmaxf(m, __shfl_xor(m, 32, 64));
+    if (BV < 16) m = fmaxf(m, __shfl_xor(m, 8, 64));
+    if (BV < 8) m = fmaxf(m, __shfl_xor(m, 4, 64));
     const int e = stage_exponent(__float_as_uint(m));
     const float sc = __builtin_ldexpf(1.0f, e);
-    if (live) {
-      for (int d0 = lr; d0 < nd; d0 += 8 * tpr) {
-        uint32_t v[8];
+    unscale = __builtin_ldexpf(1.0f, -e);
+    if (MODE == 1) unscale *= *Gp;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = d0 + u * tpr < nd ? row[d0 + u * tpr] : 0u;
+    for (int u = 0; u < CPW; ++u)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int d = d0 + u * tpr;
-          if (d < nd) row[d] = (int64_t)c0 * 128 + 2 * d < K ? to_h2(v[u], sc) : 0u;
+      for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          const uint32_t h = __builtin_bit_cast(
+              uint32_t, __builtin_amdgcn_cvt_pkrtz(bf16_lo(xr[u][v][d]) * sc, bf16_hi(xr[u][v][d]) * sc));
+          // lane j < BV collects the parts of lanes j + BV, .. (the others'
+          // MFMA columns are never stored)
+          xr[u][v][d] = h;
+          if constexpr (BV < 16) xr[u][v + NV][d] = row_rotate<BV>(h);
+          if constexpr (BV < 8) {
+            xr[u][v + 2 * NV][d] = row_rotate<2 * BV>(h);
+            xr[u][v + 3 * NV][d] = row_rotate<3 * BV>(h);
+          }
         }
-      }
-      if (lr == 0) s_small[b] = __float_as_uint(__builtin_ldexpf(1.0f, -e));
-    }
-  }
-  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  float unscale = xlane ? __uint_as_float(s_small[j]) : 1.0f;
-  if (MODE == 1) unscale *= *Gp;
-  uint4_t grid_tab{0u, 0u, 0u, 0u};
-  if (MODE == 1) {
-    if (BITS == 3)
-      grid_tab = *reinterpret_cast<const uint4_t*>(s_small + 16);
-    else
-      grid_tab = uint4_t{s_small[16], s_small[17], 0u, 0u};
-  }
-  auto tile_table = [&](int t) {
-    if (MODE == 1) return grid_tab;
-    const uint8_t* tp = tabs + t * kTabBytes + i * 2 * (1 << BITS);   // t < TI KiB / kTabBytes
-    if (BITS == 3) return *reinterpret_cast<const uint4_t*>(tp);
-    const uint2_t d = *reinterpret_cast<const uint2_t*>(tp);
-    return uint4_t{d[0], d[1], 0u, 0u};
   };
 
-  // ---- 3. slots
+  // ---- 4. tiles
   uint32_t tl0, tl1, th0, th1;
-  table_pools<BITS>(tile_table(0), tl0, tl1, th0, th1);
-  float4_t pacc[4];
+  if (MODE == 1) table_pools<BITS>(load_table<BITS>(lut), tl0, tl1, th0, th1);
+  int parked = 0;   // tiles in LDS
+  bool first = true, last = false;   // first and last pass
+  auto tile = [&](int t, auto rc) __attribute__((always_inline)) {
+    constexpr int r = decltype(rc)::value;
+    if (MODE == 0) table_pools<BITS>(tab[r], tl0, tl1, th0, th1);
+    float4_t acc;   // one chain: a chunk's lookups cover the MFMA latency
 #pragma unroll
-  for (int st = 0; st < 4; ++st) pacc[st] = float4_t{0.f, 0.f, 0.f, 0.f};
-  const _Float16* xrow = xs + (xlane ? j : 0) * rowstride + 32 * q;
-  // read the slice once before the loop: the compiler then settles its wait
-  // for the copies into LDS here, not at the top of every ring cycle
-  {
-    const uint32_t probe = *reinterpret_cast<const uint32_t*>(xrow);
-    asm volatile("" ::"v"(probe));
-  }
-  const int total = ntw * nc;
-  int ti_ = 0, u = 0;
-  auto slot = [&](const int r) __attribute__((always_inline)) {
-      half8_t bf[4];
-      const half8_t* xp = reinterpret_cast<const half8_t*>(xrow + u * 128);
-#pragma unroll
-      for (int st = 0; st < 4; ++st) bf[st] = xp[st];
-      const uint32_t sv = sring[r];
+    for (int u = 0; u < CPW; ++u) {
       uint32_t sel[8];
-      selectors<BITS>(ring[r], sel);
-      load_next(r);
+      selectors<BITS>(ring[r][u], sel);
       half2_t s_lo, s_hi;
       if (MODE == 1) {
-        const half2_t sc2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(sv, 1.0f, false);
+        const half2_t sc2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(sring[r][u] >> (8 * (lane_scale & 3)), 1.0f, false);
         s_lo = half2_t{sc2[0], sc2[0]};
         s_hi = half2_t{sc2[1], sc2[1]};
       }
+      if (u == 0 || u < nu) {   // (a wavefront without chunks multiplies zeros)
 #pragma unroll
-      for (int st = 0; st < 4; ++st) {
-        uint32_t a0, a1, a2, a3;
-        lookup4(sel[2 * st], tl0, tl1, th0, th1, a0, a1);
-        lookup4(sel[2 * st + 1], tl0, tl1, th0, th1, a2, a3);
-        half8_t af = as_half8(a0, a1, a2, a3);
-        if (MODE == 1) af = scale_half8(af, st < 2 ? s_lo : s_hi);
-        pacc[st] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af, bf[st], pacc[st], 0, 0, 0);
+        for (int st = 0; st < 4; ++st) {
+          __builtin_amdgcn_sched_barrier(0);   // one sub-step's operands at a time (registers)
+          uint32_t a0, a1, a2, a3;
+          lookup4(sel[2 * st], tl0, tl1, th0, th1, a0, a1);
+          lookup4(sel[2 * st + 1], tl0, tl1, th0, th1, a2, a3);
+          half8_t af = as_half8(a0, a1, a2, a3);
+          if (MODE == 1) af = scale_half8(af, st < 2 ? s_lo : s_hi);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(af, __builtin_bit_cast(half8_t, xr[u][st]),
+                                                       u == 0 && st == 0 ? float4_t{0.f, 0.f, 0.f, 0.f} : acc, 0, 0, 0);
+        }
       }
-      if (__builtin_expect(++u == nc, 0)) {   // end of tile ti_: lane (q, j) stores rows 4q..4q+3 of batch row j
-        u = 0;
-        float4_t acc;
+      // refill once the codes are used up: issued any earlier, the load needs
+      // other registers, and moving them back waits for every load
+      __builtin_amdgcn_sched_barrier(0);
+      if (u == 0) load_tab(t + kAhead, r);
+      load_chunk(t + kAhead, r, u);
+    }
+    float4_t sum;
 #pragma unroll
-        for (int r2 = 0; r2 < 4; ++r2)
-          acc[r2] = ((pacc[0][r2] + pacc[1][r2]) + (pacc[2][r2] + pacc[3][r2])) * unscale;
+    for (int r2 = 0; r2 < 4; ++r2) sum[r2] = acc[r2] * unscale;
+    float4_t* slot = part + (parked * W + wave) * 64 + lane;
+    if (!first) {
+      const float4_t o = *slot;
 #pragma unroll
-        for (int st = 0; st < 4; ++st) pacc[st] = float4_t{0.f, 0.f, 0.f, 0.f};
-        if (xlane) {
-          const int64_t tile = tw + ti_;
-          if (KG == 1) {
+      for (int r2 = 0; r2 < 4; ++r2) sum[r2] += o[r2];
+    }
+    *slot = sum;
+    if (++parked == park || t + 1 == nt) {   // uniform over the workgroup
+      if (!last) {   // more passes: every tile of the workgroup is parked
+        parked = 0;
+        return;
+      }
+      __syncthreads();
+      for (int p = wave; p < parked; p += W) {
+        const float4_t* pr = part + (size_t)p * W * 64 + lane;
+        float4_t o = pr[0];
+#pragma unroll 4
+        for (int w2 = 1; w2 < W; ++w2) {
+          const float4_t t2 = pr[w2 * 64];
+#pragma unroll
+          for (int r2 = 0; r2 < 4; ++r2) o[r2] += t2[r2];
+        }
+        if (xlane) {   // lane (q, j): rows 4q .. 4q + 3 of batch row j
+          const int64_t tg_ = t0 + t + 1 - parked + p;
+          if (KG > 1) {
+            *reinterpret_cast<float4_t*>(partials + (((int64_t)kg * T + tg_) * B + j) * 16 + 4 * q) = o;
+          } else {
 #pragma unroll
             for (int r2 = 0; r2 < 4; ++r2) {
-              const int64_t row = tile * 16 + 4 * q + r2;
+              const int64_t row = tg_ * 16 + 4 * q + r2;
               if (row < N) {
                 const int64_t o2 = (int64_t)j * N + row;
                 if (out_kind == 0)
-                  reinterpret_cast<float*>(y)[o2] = acc[r2];
+                  reinterpret_cast<float*>(y)[o2] = o[r2];
                 else
-                  reinterpret_cast<uint16_t*>(y)[o2] = (uint16_t)f32_to_bf16_rne(acc[r2]);
+                  reinterpret_cast<uint16_t*>(y)[o2] = (uint16_t)f32_to_bf16_rne(o[r2]);
               }
             }
-          } else {
-            *reinterpret_cast<float4_t*>(partials + (((int64_t)kg * T + tile) * B + j) * 16 + 4 * q) = acc;
           }
         }
-        ++ti_;
-        if (ti_ < ntw) table_pools<BITS>(tile_table(ti_), tl0, tl1, th0, th1);
       }
+      parked = 0;
+      if (t + 1 < nt) __syncthreads();   // the parked tiles have been read
+    }
   };
-  // whole ring cycles without exits, then the remaining slots (see the
-  // batch-1 kernel); wave priority falls with progress
-  const int full = total / RING * RING;
-  const int q1 = total / 4, q2 = total / 2, q3 = (3 * total) / 4;
-  // one loop per priority level (s_setprio takes an immediate), so that the
-  // cycles carry no branches for it
-  int f0 = 0;
-  for (; f0 < full && f0 < q1; f0 += RING) {
-#pragma unroll
-    for (int r = 0; r < RING; ++r) slot(r);
+  static_assert(kAhead == 2, "two tiles per loop");
+  for (; !last; first = false, cp += W * CPW) {
+    nu = min(CPW, (c0 + nc - cp - wave + W - 1) / W);
+    last = c0 + nc - cp <= W * CPW;
+    load_pass();
+    int t = 0;
+    for (; t + 2 <= nt; t += 2) {
+      tile(t, std::integral_constant<int, 0>{});
+      tile(t + 1, std::integral_constant<int, 1>{});
+    }
+    if (t < nt) tile(t, std::integral_constant<int, 0>{});
   }
-  __builtin_amdgcn_s_setprio(2);
-  for (; f0 < full && f0 < q2; f0 += RING) {
-#pragma unroll
-    for (int r = 0; r < RING; ++r) slot(r);
-  }
-  __builtin_amdgcn_s_setprio(1);
-  for (; f0 < full && f0 < q3; f0 += RING) {
-#pragma unroll
-    for (int r = 0; r < RING; ++r) slot(r);
-  }
-  __builtin_amdgcn_s_setprio(0);
-  for (; f0 < full; f0 += RING) {
-#pragma unroll
-    for (int r = 0; r < RING; ++r) slot(r);
-  }
-#pragma unroll
-  for (int r = 0; r < RING - 1; ++r)
-    if (full + r < total) slot(r);
 }
 
-// y[jj][row] = sum over the K groups, in order, of the split kernel's
+// y[jj][row] = sum over the K groups, in order, of the batched kernel's
 // partials [KG][T][B][16]
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ partials, int KG, int T, int B,
                                                               int64_t N, int out_kind, void* __restrict__ y) {
@@ -1125,82 +1107,100 @@ inline int persist_wgs_per_cu(int vgprs, int waves, int64_t lds) {
   return std::max(1, std::min(by_vgpr, by_lds));
 }
 
-// Wavefront tasks per compute unit for the batched kernel.  Fewer tasks mean
-// fewer K groups: less partial-sum traffic and less activation staging per
-// weight byte, but fewer wavefronts streaming.  Measured over the 27B block
-// (q/k/v, o, gate/up, down), one call each in a captured graph: at batch 8,
-// 12 tasks 5 % faster than 6 in total (gate/up and down gain, the small
-// matrices lose); at batch 16, 6 tasks 12 % faster than 12 (the activation
-// staging of a K group grows with the batch); 24 and 48 slower everywhere.
-// (Timed alone, 64 calls of one matrix in a row, q/k/v and o at batch 8 run
-// faster with 6 tasks; in the token's order of matrices they do not.)
-inline int64_t gemv_tasks_per_cu(int64_t B) { return B >= 12 ? 6 : 12; }
+// K groups whose partial sums the workspace of a batch B >= 2 call holds (the
+// size that callers query, and the limit of the no-allocation variant): the
+// plan below uses at most these.
+inline int64_t contract_groups(int64_t B, int64_t T, int64_t KC) {
+  const int64_t tasks = (int64_t)num_cus() * (B >= 12 ? 6 : 12);
+  const int64_t by_slice = std::max<int64_t>(1, (40 * 1024) / (B * 256));
+  const int64_t KG = std::max<int64_t>((KC + by_slice - 1) / by_slice, std::min<int64_t>(KC, (tasks + T - 1) / T));
+  const int64_t KCR = (KC + KG - 1) / KG;
+  return (KC + KCR - 1) / KCR;
+}
 
-// Plan of the batch B >= 2 split-K kernel (see lut_gemv_split_kernel).
+// Plan of the batch B >= 2 kernel (see lut_gemv_batch_kernel).
 struct BatchedPlan {
-  bool ok;               // false: the codes exceed the kernel's 32-bit offsets
-  int64_t KG, KCR, TPW;  // K groups, chunks per K group, tiles per wavefront
-  int64_t TI, G, lds;    // table KiB per wavefront, workgroups, LDS bytes
-  size_t partial_bytes;  // K-group partial sums (0 when KG == 1)
+  bool ok;                   // false: the matrix exceeds the kernel's 32-bit offsets
+  int64_t W, CPW;            // wavefronts per workgroup, chunks per wavefront and pass
+  int64_t KG, KCR, TPG, G;   // K groups, chunks per group, tiles per workgroup, workgroups
+  int64_t park;              // tiles parked in LDS
 };
 
+inline bool batched_ok(int bits, int64_t T, int64_t KC) {
+  return T * KC * 64 * (bits == 3 ? 12 : 8) < ((int64_t)1 << 31);
+}
+
 inline BatchedPlan plan_batched(int bits, int64_t B, int64_t T, int64_t KC) {
-  constexpr int kW = 8;
-  const int64_t tab_bytes = 32 << bits;
   BatchedPlan p{};
-  p.ok = T * KC * 64 * (bits == 3 ? 12 : 8) < ((int64_t)1 << 31);
-  // wavefront tasks (one tile over one K group) per compute unit; a K
-  // group's slice of x stays within ~40 KiB of LDS
-  const int64_t tasks = (int64_t)num_cus() * gemv_tasks_per_cu(B);
-  const int64_t kcr_lds = std::max<int64_t>(1, (40 * 1024) / (B * 256));
-  int64_t KG = std::max<int64_t>((KC + kcr_lds - 1) / kcr_lds, std::min<int64_t>(KC, (tasks + T - 1) / T));
-  p.KCR = (KC + KG - 1) / KG;
+  p.ok = batched_ok(bits, T, KC) && B * KC * 256 < ((int64_t)1 << 31);
+  // sixteen wavefronts of at most three chunks (48 activation registers, of
+  // the 128 that leave four wavefronts per SIMD).  Short rows take fewer
+  // wavefronts and as many more workgroups per compute unit: with several
+  // tiles per workgroup as few as hold the row (two or three chunks share a
+  // tile's set-up: 65536 x 1056 at batch 2 14.7 -> 9.9 us), else one chunk
+  // each.  More than 48 chunks: K groups, or passes where the workspace holds
+  // too few groups.
+  const int64_t cus = num_cus();
+  const bool deep = T >= 2 * cus;
+  p.W = deep ? (KC > 24 ? 16 : KC > 12 ? 8 : 4) : (KC > 8 ? 16 : KC > 4 ? 8 : 4);
+  const int64_t fit = 3 * p.W, most = contract_groups(B, T, KC);
+  p.KG = std::min((KC + fit - 1) / fit, most);
+  // few tiles: more K groups use the idle compute units and leave each less of
+  // x to convert, which pays for the reduction pass where there is one anyway
+  // or the batch is large (batch 16: 512 x 12288 11.9 -> 8.2 us, 2048 x 6144
+  // 10.1 -> 9.5)
+  if (T * p.KG <= cus && (p.KG > 1 || (B > 8 && KC > 40)))
+    p.KG = std::min(most, std::max(p.KG, std::min((KC + p.W - 1) / p.W, (B > 8 ? 2 : 1) * cus / T)));
+  p.KCR = (KC + p.KG - 1) / p.KG;
   p.KG = (KC + p.KCR - 1) / p.KCR;
-  p.TPW = std::min<int64_t>(16, std::max<int64_t>(1, T * p.KG / tasks));
-  p.TI = (p.TPW * tab_bytes + 1023) / 1024;
-  const int64_t TG = (T + kW * p.TPW - 1) / (kW * p.TPW);
-  p.G = p.KG * TG;
-  p.lds = round_up(B * (p.KCR * 128 + 8) * 2, 16) + kW * p.TI * 1024;
-  p.partial_bytes = p.KG > 1 ? (size_t)(p.KG * T * B * 16 * 4) : 0;
+  const int64_t passes = (p.KCR + fit - 1) / fit;
+  p.CPW = (p.KCR + passes * p.W - 1) / (passes * p.W);
+  const int64_t slots = cus * (16 / p.W), fits = kParkBytes / (16 * 1024);   // W KiB a tile, 16 / W workgroups
+  int64_t groups = std::min<int64_t>(T, std::max<int64_t>(1, slots / p.KG));
+  if (passes > 1)   // every tile stays parked over the passes: whole rounds of fuller workgroups
+    groups *= (T + groups * fits - 1) / (groups * fits);
+  p.TPG = (T + groups - 1) / groups;
+  p.G = (T + p.TPG - 1) / p.TPG * p.KG;
+  p.park = std::min<int64_t>(p.TPG, fits);
   return p;
 }
 
-// Batch B >= 2: split-K kernel, and with more than one K group a reduction
+// Batch B >= 2: the batched kernel, and with more than one K group a reduction
 // pass over the K-group partials, held in the caller's workspace `ws` (at
-// least plan.partial_bytes) or, when ws is NULL, in stream-ordered staging
+// least gemv_workspace_bytes) or, when ws is NULL, in stream-ordered staging
 // from the library's pool.  Returns hipErrorNotSupported when the matrix is
 // too large for the kernel's 32-bit offsets.
 template <int BITS, int MODE>
 hipError_t launch_gemv_batched(const uint16_t* x, int64_t B, const LutView& w, int out_kind, void* y, void* ws,
                                hipStream_t s, int64_t T, int64_t KC) {
-  constexpr int kW = 8;
   const int64_t N = w.rows, K = w.cols;
   const BatchedPlan p = plan_batched(BITS, B, T, KC);
   if (!p.ok) return hipErrorNotSupported;
   typedef void (*kern_t)(const uint16_t*, int64_t, int, const uint8_t*, const uint16_t*, const uint8_t*,
-                         const float*, int64_t, SplitPlan, float*, int, void*);
-  kern_t kern;
-  switch (MODE == 1 ? 1 : p.TI) {
-    case 1: kern = lut_gemv_split_kernel<BITS, MODE, kRingPersist, 1>; break;
-    case 2: kern = lut_gemv_split_kernel<BITS, MODE, kRingPersist, 2>; break;
-    case 3: kern = lut_gemv_split_kernel<BITS, MODE, kRingPersist, 3>; break;
-    default: kern = lut_gemv_split_kernel<BITS, MODE, kRingPersist, 4>; break;
-  }
+                         const float*, int64_t, BatchPlan, int, float*, int, void*);
+  static const kern_t kerns[3][3] = {
+      {lut_gemv_batch_kernel<BITS, MODE, 1, 4>, lut_gemv_batch_kernel<BITS, MODE, 1, 8>, lut_gemv_batch_kernel<BITS, MODE, 1, 16>},
+      {lut_gemv_batch_kernel<BITS, MODE, 2, 4>, lut_gemv_batch_kernel<BITS, MODE, 2, 8>, lut_gemv_batch_kernel<BITS, MODE, 2, 16>},
+      {lut_gemv_batch_kernel<BITS, MODE, 3, 4>, lut_gemv_batch_kernel<BITS, MODE, 3, 8>, lut_gemv_batch_kernel<BITS, MODE, 3, 16>}};
+  const kern_t kern = kerns[p.CPW - 1][B > 8 ? 2 : B > 4 ? 1 : 0];
+  const size_t lds = (size_t)(p.park * p.W * 1024);
   float* partials = reinterpret_cast<float*>(ws);
   const bool pooled = p.KG > 1 && partials == nullptr;
-  hipError_t e = hipSuccess;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)lds);
+  if (e != hipSuccess) return e;
   if (pooled) {
-    e = pool_alloc_async(reinterpret_cast<void**>(&partials), p.partial_bytes, s);
+    e = pool_alloc_async(reinterpret_cast<void**>(&partials), (size_t)(p.KG * T * B * 16 * 4), s);
     if (e != hipSuccess) return e;
   }
-  SplitPlan sp{};
-  sp.KG = (int)p.KG;
-  sp.TPW = (int)p.TPW;
-  sp.KCR = (int)p.KCR;
-  sp.tiles = (int)T;
-  sp.KC = (int)KC;
-  hipLaunchKernelGGL(kern, dim3((unsigned)p.G), dim3(kW * 64), (size_t)p.lds, s, x, K, (int)B, w.codes, w.lut,
-                     w.scales, w.G, N, sp, partials, out_kind, y);
+  BatchPlan bp{};
+  bp.KG = (int)p.KG;
+  bp.KCR = (int)p.KCR;
+  bp.TPG = (int)p.TPG;
+  bp.tiles = (int)T;
+  bp.KC = (int)KC;
+  hipLaunchKernelGGL(kern, dim3((unsigned)p.G), dim3((unsigned)(p.W * 64)), lds, s, x, K, (int)B, w.codes, w.lut,
+                     w.scales, w.G, N, bp, (int)p.park, partials, out_kind, y);
   e = hipGetLastError();
   if (p.KG > 1 && e == hipSuccess) {
     const int64_t n = T * B * 16;
@@ -1360,8 +1360,9 @@ hipError_t gemv_noalloc_scratch(void** ptr) {
 
 size_t gemv_workspace_bytes(int64_t B, const LutView& w) {
   if (B < 2 || w.rows == 0 || w.cols == 0) return 0;
-  const BatchedPlan p = plan_batched(w.bits, B, round_up(w.rows, 16) / 16, round_up(w.cols, 128) / 128);
-  return p.ok ? p.partial_bytes : 0;
+  const int64_t T = round_up(w.rows, 16) / 16, KC = round_up(w.cols, 128) / 128;
+  const int64_t KG = batched_ok(w.bits, T, KC) ? contract_groups(B, T, KC) : 1;
+  return KG > 1 ? (size_t)(KG * T * B * 16 * 4) : 0;
 }
 
 hipError_t launch_gemv(const uint16_t* x, int64_t B, const LutView& w, int out_kind, void* y, void* ws,
