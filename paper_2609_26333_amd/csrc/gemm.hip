@@ -611,9 +611,13 @@ __global__ __launch_bounds__(64 * Gm::waves, Gm::waves / 4) void nvfp4_gemm_shor
   extern __shared__ __align__(16) uint8_t smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // workgroup b runs on XCD b % 8, where it takes the row panels of one column
-  // panel in turn: a weight tile is read from memory into one L2
-  const int bm = (int)(blockIdx.x >> 3) % tiles_m, bn = ((int)(blockIdx.x >> 3) / tiles_m) * 8 + (int)(blockIdx.x & 7);
+  // Workgroup b runs on XCD b % 8; each XCD takes an equal run of the tiles,
+  // row panels fastest, so that a weight tile is read from memory into one L2
+  // (two at the ends of a run).  Whole column panels per XCD left some of them
+  // with a round more than others: 2092 x 1680 x 10304 with its quantizer
+  // 110 us, now 83 (ring kernels 94).
+  const int id = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  const int bm = id % tiles_m, bn = id / tiles_m;
   if (bn >= tiles_n) return;
   const int64_t m0 = (int64_t)bm * 32 * TM, n0 = (int64_t)bn * 32 * TN;
   const int kt0 = wave * SPW;
@@ -781,7 +785,7 @@ hipError_t launch_short(const GemmArgs& a, hipStream_t s) {
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)Gm::lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * round_up(tiles_n, 8))), dim3(64 * Gm::waves), Gm::lds, s, a.A.codes,
+  hipLaunchKernelGGL(kern, dim3((unsigned)round_up((int64_t)tiles_m * tiles_n, 8)), dim3(64 * Gm::waves), Gm::lds, s, a.A.codes,
                      a.A.scales, a.A.G, a.W.codes, a.W.scales, a.W.G, a.M, (int)(round_up(a.M, 32) / 32),
                      (int)(round_up(a.N, 32) / 32), KT, tiles_m, tiles_n, (KT + Gm::waves - 1) / Gm::waves,
                      gemm_out(a));
@@ -830,7 +834,8 @@ hipError_t launch_geo(const GemmArgs& a, int64_t split, hipStream_t s) {
 // Modelled time (us) of a grid, for the choice between the kernels.  Both
 // sides were measured on 230 combinations of M = 16 .. 4096 with the 8B and
 // 27B linears and 1024 x 4096, 1024 x 16384, 3072 x 768; the model is within
-// 7-10 % of either, and the choice within 1 % of the faster kernel on average.
+// 7-10 % of either, and the choice within 1 % of the faster kernel on average
+// (on 460 random shapes up to 8192 rows, within 1.8 % of the fastest of all).
 // Ring kernels: per K step, by resident workgroups (1 or 2 per compute unit)
 // and then by the total of 256 x 128 tiles.
 double ring_time(int64_t M, int64_t N, int64_t KT, int64_t cus) {
