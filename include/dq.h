@@ -278,8 +278,9 @@ dq_status dq_autocast_lut_to_nvfp4(const dq_lut_t* W, const float* G_override, c
  * and needs no workspace (dq_decode_gemv_nvfp4_workspace_size reports 0);
  * otherwise
  * workspace / workspace_bytes are as for dq_decode_gemv (partial sums over K
- * groups; NULL takes stream-ordered memory from the library's pool).
- * Activations are staged as fp16 after a power-of-two rescale per batch row
+ * groups, where a row is split over workgroups; NULL takes stream-ordered
+ * memory from the library's pool).
+ * Activations are used as fp16 after a power-of-two rescale per batch row
  * and K slice (the conversion described for dq_decode_gemv); weight products
  * are exact, sums fp32. */
 dq_status dq_decode_gemv_nvfp4_workspace_size(int64_t B, const dq_nvfp4_t* W, size_t* bytes);

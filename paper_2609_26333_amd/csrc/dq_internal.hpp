@@ -120,6 +120,10 @@ inline int64_t gemm_column_split(int64_t M, int64_t N, int64_t bm_full, int64_t 
 size_t gemv_nvfp4_workspace_bytes(int64_t B, int64_t N, int64_t K);
 hipError_t launch_gemv_nvfp4(const uint16_t* x, int64_t B, const NvFp4View& w, int out_kind, void* y, void* ws,
                              hipStream_t s);
+// The batched kernel of gemv.hip on NVFP4 weights (K > 0); its K groups use at
+// most ws_bytes of workspace.  hipErrorNotSupported: too large for its offsets.
+hipError_t launch_gemv_nvfp4_batched(const uint16_t* x, int64_t B, const NvFp4View& w, int out_kind, void* y, void* ws,
+                                     size_t ws_bytes, hipStream_t s);
 
 // a6: LUT GEMV (gemv.hip).  ws: workspace of at least
 // gemv_workspace_bytes(B, w) bytes, or NULL to take it from the pool.

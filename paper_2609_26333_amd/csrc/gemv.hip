@@ -62,6 +62,24 @@ struct CodeVec<2> {
   typedef Group2 type;
   static constexpr int bytes = 8;
 };
+// NVFP4 (batched kernel): 16 E2M1 codes of each of a chunk's two K steps
+struct Group4 {
+  uint32_t w[4];
+};
+template <>
+struct CodeVec<4> {
+  typedef Group4 type;
+  static constexpr int bytes = 16;
+};
+
+// 8 E2M1 codes times an fp16 block scale: 8 exact fp16 values
+__device__ inline half8_t e2m1_scaled8(uint32_t w, half2_t s) {
+  const half2_t p0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 0) * s;
+  const half2_t p1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 1) * s;
+  const half2_t p2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 2) * s;
+  const half2_t p3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 3) * s;
+  return half8_t{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
+}
 
 // fp16 pair from the low-byte and high-byte lookups of four codes
 __device__ inline void lookup4(uint32_t sel, uint32_t tl0, uint32_t tl1, uint32_t th0, uint32_t th1,
@@ -686,9 +704,17 @@ constexpr int kRingMulti = 8;
 // two barriers, a reduction launch for each matrix): 27B block, LUT3, batch 2
 // 60.8 -> 46.1 us, 8 66.6 -> 51.5, 16 70.9 -> 59.8; LUT2 with block scales at
 // batch 8 70.7 -> 55.5; 12288 x 4096 at batch 4 11.4 -> 8.3.
+// MODE 2: NVFP4 weights (32 x 64 tiles of E2M1 codes with an E4M3 scale per 16
+// columns).  A row tile is half of theirs and a chunk two K steps of it, so a
+// lane's two pieces of 8 bytes are each one scale block (columns 16q .. 16q +
+// 15 of the step) and the loads stay contiguous over the wavefront.  Bound:
+// the code stream (34816 x 5120, 100 MB: 24.2 us = 4.1 TB/s).  Against K
+// slices of x staged in LDS and a reduction launch: 27B block at batch 4 73.8
+// -> 63.6 us, 16 107 -> 84; 12288 x 4096 at batch 4 13.1 -> 9.1.
 struct BatchPlan {
   int KG, KCR, TPG;   // K groups, chunks per K group, tiles per workgroup
   int tiles, KC;
+  int KT;             // NVFP4: K steps of 64 columns
 };
 typedef uint16_t ushort2_t __attribute__((ext_vector_type(2)));
 constexpr int kAhead = 2;   // tiles of codes in flight per wavefront
@@ -730,20 +756,36 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
   const i32x4_t rx = buffer_resource(x, (uint32_t)((int64_t)B * K * 2));
   // ---- 2. tables and codes of the first tiles (past the last tile, and past
   // the wavefront's last chunk: nothing is read)
-  const i32x4_t rcodes = buffer_resource(codes, (uint32_t)T * (uint32_t)KC * kChunkBytes);
+  // (NVFP4: tiles of 32 rows x 64 columns, addressed from the workgroup's first)
+  const int p0 = t0 >> 1, np = ((t0 + nt + 1) >> 1) - p0;
+  const i32x4_t rcodes = MODE == 2 ? buffer_resource(codes + (int64_t)p0 * plan.KT * 1024, (uint32_t)(np * plan.KT) * 1024)
+                                   : buffer_resource(codes, (uint32_t)T * (uint32_t)KC * kChunkBytes);
   const i32x4_t rtab = buffer_resource(lut, (uint32_t)(T * kTabBytes));   // PER_ROW
   i32x4_t rscales{};
   if (MODE == 1) rscales = buffer_resource(scales, (uint32_t)T * (uint32_t)KC * 128);
-  const int32_t lane_code = lane * CodeVec<BITS>::bytes, lane_scale = lane * 2, lane_tab = i * 2 * (1 << BITS);
+  if (MODE == 2) rscales = buffer_resource(scales + (int64_t)p0 * plan.KT * 128, (uint32_t)(np * plan.KT) * 128);
+  const int32_t lane_code = MODE == 2 ? 32 * i + 8 * q : lane * CodeVec<BITS>::bytes, lane_scale = lane * 2, lane_tab = i * 2 * (1 << BITS);
   cvec ring[kAhead][CPW];
-  uint32_t sring[kAhead][CPW];
+  uint32_t sring[kAhead][CPW][2];
   uint4_t tab[kAhead];
   int cp = c0, nu = 0;   // this pass: first chunk, chunks of this wavefront (<= CPW)
   auto load_chunk = [&](int t, int r, int u) {
     const bool ok = t < nt && u < nu;
     const int cidx = (t0 + t) * KC + cp + u * W + wave;   // (out of range: not read, whatever it is)
     const int32_t vc = ok ? lane_code : kNowhere - 64;
-    if constexpr (BITS == 3) {
+    if constexpr (MODE == 2) {
+      const int st0 = 2 * (cp + u * W + wave), half = (t0 + t) & 1;
+      const int step = (((t0 + t) >> 1) - p0) * plan.KT + st0;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const bool in = ok && st0 + h < plan.KT;
+        const i32x2_t v = raw_buffer_load_b64(rcodes, in ? lane_code : kNowhere - 64, (step + h) * 1024 + half * 512, 0);
+        ring[r][u].w[2 * h] = (uint32_t)v[0];
+        ring[r][u].w[2 * h + 1] = (uint32_t)v[1];
+        sring[r][u][h] =
+            (uint32_t)raw_buffer_load_b32(rscales, in ? 4 * i : kNowhere - 64, (step + h) * 128 + half * 64, 0);
+      }
+    } else if constexpr (BITS == 3) {
       const i32x3_t v = raw_buffer_load_b96(rcodes, vc, cidx * kChunkBytes, 0);
       ring[r][u] = cvec{{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2]}};
     } else {
@@ -751,10 +793,10 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
       ring[r][u] = cvec{{(uint32_t)v[0], (uint32_t)v[1]}};
     }
     if (MODE == 1)
-      sring[r][u] = (uint32_t)raw_buffer_load_b32(rscales, ok ? lane_scale & ~3 : kNowhere - 64, cidx * 128, 0);
+      sring[r][u][0] = (uint32_t)raw_buffer_load_b32(rscales, ok ? lane_scale & ~3 : kNowhere - 64, cidx * 128, 0);
   };
   auto load_tab = [&](int t, int r) {
-    if constexpr (MODE == 1) return;
+    if constexpr (MODE != 0) return;
     const int32_t off = t < nt ? (t0 + t) * kTabBytes + lane_tab : kNowhere - 64;
     if constexpr (BITS == 3) {
       const i32x4_t v = raw_buffer_load_b128(rtab, off, 0, 0);
@@ -772,11 +814,18 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
   auto load_pass = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < CPW; ++u) {
-      const int64_t k = (int64_t)(cp + u * W + wave) * 128 + 32 * q;   // K % 32 == 0: all 32 columns inside, or none
-      const int32_t off = u < nu && jx < B && k < K ? (int32_t)((jx * K + k) * 2) + j / BV * (NV * 16) : kNowhere - 64;
+      // LUT, K % 32 == 0: the lane's 32 columns are all inside, or none; NVFP4,
+      // K % 16 == 0: 16 columns of each K step
+      const int64_t k = (int64_t)(cp + u * W + wave) * 128 + (MODE == 2 ? 16 : 32) * q;
+      const bool in = u < nu && jx < B && k < K, in2 = MODE == 2 ? u < nu && jx < B && k + 64 < K : in;
+      const int32_t base = (int32_t)((jx * K + k) * 2);
+      const int32_t off_lut = in ? base + j / BV * (NV * 16) : kNowhere - 64;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        const i32x4_t w = raw_buffer_load_b128(rx, off + 16 * v, 0, 0);
+        const int vv = j / BV * NV + v;   // NVFP4: 16-byte piece of the lane's columns
+        const int32_t off = MODE != 2 ? off_lut + 16 * v
+                                      : (vv >> 1 ? in2 : in) ? base + 128 * (vv >> 1) + 16 * (vv & 1) : kNowhere - 64;
+        const i32x4_t w = raw_buffer_load_b128(rx, off, 0, 0);
         xr[u][v] = uint4_t{(uint32_t)w[0], (uint32_t)w[1], (uint32_t)w[2], (uint32_t)w[3]};
       }
     }
@@ -803,7 +852,7 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
     const int e = stage_exponent(__float_as_uint(m));
     const float sc = __builtin_ldexpf(1.0f, e);
     unscale = __builtin_ldexpf(1.0f, -e);
-    if (MODE == 1) unscale *= *Gp;
+    if (MODE != 0) unscale *= *Gp;
 #pragma unroll
     for (int u = 0; u < CPW; ++u)
 #pragma unroll
@@ -835,22 +884,33 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
 #pragma unroll
     for (int u = 0; u < CPW; ++u) {
       uint32_t sel[8];
-      selectors<BITS>(ring[r][u], sel);
+      if constexpr (MODE != 2) selectors<BITS>(ring[r][u], sel);
       half2_t s_lo, s_hi;
       if (MODE == 1) {
-        const half2_t sc2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(sring[r][u] >> (8 * (lane_scale & 3)), 1.0f, false);
+        const half2_t sc2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(sring[r][u][0] >> (8 * (lane_scale & 3)), 1.0f, false);
         s_lo = half2_t{sc2[0], sc2[0]};
         s_hi = half2_t{sc2[1], sc2[1]};
+      }
+      if (MODE == 2) {
+        const half2_t a = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(sring[r][u][0] >> (8 * q), 1.0f, false);
+        const half2_t b = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(sring[r][u][1] >> (8 * q), 1.0f, false);
+        s_lo = half2_t{a[0], a[0]};
+        s_hi = half2_t{b[0], b[0]};
       }
       if (u == 0 || u < nu) {   // (a wavefront without chunks multiplies zeros)
 #pragma unroll
         for (int st = 0; st < 4; ++st) {
           __builtin_amdgcn_sched_barrier(0);   // one sub-step's operands at a time (registers)
-          uint32_t a0, a1, a2, a3;
-          lookup4(sel[2 * st], tl0, tl1, th0, th1, a0, a1);
-          lookup4(sel[2 * st + 1], tl0, tl1, th0, th1, a2, a3);
-          half8_t af = as_half8(a0, a1, a2, a3);
-          if (MODE == 1) af = scale_half8(af, st < 2 ? s_lo : s_hi);
+          half8_t af;
+          if constexpr (MODE == 2) {
+            af = e2m1_scaled8(ring[r][u].w[st], st < 2 ? s_lo : s_hi);
+          } else {
+            uint32_t a0, a1, a2, a3;
+            lookup4(sel[2 * st], tl0, tl1, th0, th1, a0, a1);
+            lookup4(sel[2 * st + 1], tl0, tl1, th0, th1, a2, a3);
+            af = as_half8(a0, a1, a2, a3);
+            if (MODE == 1) af = scale_half8(af, st < 2 ? s_lo : s_hi);
+          }
           acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(af, __builtin_bit_cast(half8_t, xr[u][st]),
                                                        u == 0 && st == 0 ? float4_t{0.f, 0.f, 0.f, 0.f} : acc, 0, 0, 0);
         }
@@ -1118,7 +1178,8 @@ inline int64_t contract_groups(int64_t B, int64_t T, int64_t KC) {
   return (KC + KCR - 1) / KCR;
 }
 
-// Plan of the batch B >= 2 kernel (see lut_gemv_batch_kernel).
+// Plan of the batch B >= 2 kernel (see lut_gemv_batch_kernel), with at most
+// `most` K groups.
 struct BatchedPlan {
   bool ok;                   // false: the matrix exceeds the kernel's 32-bit offsets
   int64_t W, CPW;            // wavefronts per workgroup, chunks per wavefront and pass
@@ -1127,10 +1188,11 @@ struct BatchedPlan {
 };
 
 inline bool batched_ok(int bits, int64_t T, int64_t KC) {
+  if (bits == 4) return KC * 2048 * 4 < ((int64_t)1 << 31);   // (offsets within a workgroup's tiles only)
   return T * KC * 64 * (bits == 3 ? 12 : 8) < ((int64_t)1 << 31);
 }
 
-inline BatchedPlan plan_batched(int bits, int64_t B, int64_t T, int64_t KC) {
+inline BatchedPlan plan_batched(int bits, int64_t B, int64_t T, int64_t KC, int64_t most) {
   BatchedPlan p{};
   p.ok = batched_ok(bits, T, KC) && B * KC * 256 < ((int64_t)1 << 31);
   // sixteen wavefronts of at most three chunks (48 activation registers, of
@@ -1143,7 +1205,7 @@ inline BatchedPlan plan_batched(int bits, int64_t B, int64_t T, int64_t KC) {
   const int64_t cus = num_cus();
   const bool deep = T >= 2 * cus;
   p.W = deep ? (KC > 24 ? 16 : KC > 12 ? 8 : 4) : (KC > 8 ? 16 : KC > 4 ? 8 : 4);
-  const int64_t fit = 3 * p.W, most = contract_groups(B, T, KC);
+  const int64_t fit = 3 * p.W;
   p.KG = std::min((KC + fit - 1) / fit, most);
   // few tiles: more K groups use the idle compute units and leave each less of
   // x to convert, which pays for the reduction pass where there is one anyway
@@ -1160,6 +1222,7 @@ inline BatchedPlan plan_batched(int bits, int64_t B, int64_t T, int64_t KC) {
   if (passes > 1)   // every tile stays parked over the passes: whole rounds of fuller workgroups
     groups *= (T + groups * fits - 1) / (groups * fits);
   p.TPG = (T + groups - 1) / groups;
+  if (bits == 4) p.TPG = std::min(p.TPG, (((int64_t)1 << 31) - 4096) / (KC * 1024) - 2);
   p.G = (T + p.TPG - 1) / p.TPG * p.KG;
   p.park = std::min<int64_t>(p.TPG, fits);
   return p;
@@ -1172,9 +1235,9 @@ inline BatchedPlan plan_batched(int bits, int64_t B, int64_t T, int64_t KC) {
 // too large for the kernel's 32-bit offsets.
 template <int BITS, int MODE>
 hipError_t launch_gemv_batched(const uint16_t* x, int64_t B, const LutView& w, int out_kind, void* y, void* ws,
-                               hipStream_t s, int64_t T, int64_t KC) {
+                               hipStream_t s, int64_t T, int64_t KC, int64_t most) {
   const int64_t N = w.rows, K = w.cols;
-  const BatchedPlan p = plan_batched(BITS, B, T, KC);
+  const BatchedPlan p = plan_batched(BITS, B, T, KC, most);
   if (!p.ok) return hipErrorNotSupported;
   typedef void (*kern_t)(const uint16_t*, int64_t, int, const uint8_t*, const uint16_t*, const uint8_t*,
                          const float*, int64_t, BatchPlan, int, float*, int, void*);
@@ -1199,6 +1262,7 @@ hipError_t launch_gemv_batched(const uint16_t* x, int64_t B, const LutView& w, i
   bp.TPG = (int)p.TPG;
   bp.tiles = (int)T;
   bp.KC = (int)KC;
+  bp.KT = (int)(round_up(K, 64) / 64);
   hipLaunchKernelGGL(kern, dim3((unsigned)p.G), dim3((unsigned)(p.W * 64)), lds, s, x, K, (int)B, w.codes, w.lut,
                      w.scales, w.G, N, bp, (int)p.park, partials, out_kind, y);
   e = hipGetLastError();
@@ -1223,7 +1287,8 @@ hipError_t launch_gemv_t(const uint16_t* x, int64_t B, const LutView& w, int out
   pl.tiles = round_up(N, 16) / 16;
   pl.KC = round_up(K, 128) / 128;
   if (B >= 2) {
-    const hipError_t e = launch_gemv_batched<BITS, MODE>(x, B, w, out_kind, y, ws, s, pl.tiles, pl.KC);
+    const hipError_t e = launch_gemv_batched<BITS, MODE>(x, B, w, out_kind, y, ws, s, pl.tiles, pl.KC,
+                                                           contract_groups(B, pl.tiles, pl.KC));
     if (e != hipErrorNotSupported) return e;
   }
   // Persistent kernel whenever the staged activations leave room for at
@@ -1333,7 +1398,7 @@ pieces:
 // holds its own copy until the process ends; its device address is looked up
 // once per device (host code must never pass the array's name itself: that
 // is a host-side stand-in).  Calls that overlap on one GPU share it and race.
-// The partial sums are written in full by the split kernel before the
+// The partial sums are written in full by the batched kernel before the
 // reduction reads them, so nothing needs clearing between calls.
 constexpr size_t kNoallocScratchBytes = DQ_NOALLOC_SCRATCH_BYTES;
 static __device__ __align__(256) uint8_t scratch[kNoallocScratchBytes];
@@ -1363,6 +1428,14 @@ size_t gemv_workspace_bytes(int64_t B, const LutView& w) {
   const int64_t T = round_up(w.rows, 16) / 16, KC = round_up(w.cols, 128) / 128;
   const int64_t KG = batched_ok(w.bits, T, KC) ? contract_groups(B, T, KC) : 1;
   return KG > 1 ? (size_t)(KG * T * B * 16 * 4) : 0;
+}
+
+hipError_t launch_gemv_nvfp4_batched(const uint16_t* x, int64_t B, const NvFp4View& w, int out_kind, void* y, void* ws,
+                                     size_t ws_bytes, hipStream_t s) {
+  const int64_t T = round_up(w.rows, 16) / 16, KC = round_up(w.cols, 128) / 128;
+  const LutView v{w.codes, nullptr, w.scales, w.G, w.rows, w.cols, 4, 2};
+  return launch_gemv_batched<4, 2>(x, B, v, out_kind, y, ws, s, T, KC,
+                                   std::max<int64_t>(1, (int64_t)ws_bytes / (T * B * 16 * 4)));
 }
 
 hipError_t launch_gemv(const uint16_t* x, int64_t B, const LutView& w, int out_kind, void* y, void* ws,

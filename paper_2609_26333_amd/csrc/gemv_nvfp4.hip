@@ -14,11 +14,16 @@
 // power-of-two rescale per batch row and K group (the reading used by the
 // LUT GEMV), so every product is exact and the sums are fp32.
 //
-// Work split: a workgroup takes one K group of a group of row tiles, stages
-// that K slice of x once, and its wavefronts each stream whole tiles over the
-// K group (no reduction between wavefronts).  With more than one K group the
-// tile sums go to a workspace that a second pass adds up in K-group order
-// (deterministic).
+// Three kernels: the batched kernel of gemv.hip (activations in registers) for
+// all but two ranges, nvfp4_gemv_ks_kernel for small batches where it is still
+// the faster (see ks_better), and nvfp4_gemv_kernel for rows so wide that they
+// exceed the batched kernel's 32-bit offsets.
+//
+// nvfp4_gemv_kernel: a workgroup takes one K group of a group of row tiles,
+// stages that K slice of x once, and its wavefronts each stream whole tiles
+// over the K group (no reduction between wavefronts).  With more than one K
+// group the tile sums go to a workspace that a second pass adds up in K-group
+// order (deterministic).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -236,9 +241,9 @@ __global__ __launch_bounds__(256) void nvfp4_gemv_kernel(const uint16_t* __restr
   if (q < cycles) consume(q, cb0);
 }
 
-// One-launch kernel for small batches (B <= 8 with the staged slices within
-// 48 KiB of LDS) and at most one resident round of row tiles (16 wavefronts
-// per compute unit).  A workgroup of kKsWaves (4 or 8) wavefronts takes one
+// One-launch kernel for batch 1 and 2 (the staged slices within 48 KiB of LDS)
+// and at most one resident round of row tiles (16 wavefronts per compute
+// unit).  A workgroup of kKsWaves (4 or 8) wavefronts takes one
 // row tile;
 // wavefront w takes K steps [w SPW, (w + 1) SPW).  It copies its own slice of
 // x straight into LDS (issued before its code loads, so the copy is not
@@ -461,8 +466,24 @@ KsPlan ks_plan(int64_t B, int64_t N, int64_t K) {
   return p;
 }
 
+// Where the one-launch kernel is still faster than the batched one (measured
+// over N = 512 .. 65536, K = 512 .. 17408, batch 1 .. 16):
+// - batch 1 or 2 with one to two 16-row tiles per compute unit and more than
+//   1024 columns: the batched kernel leaves compute units without a second
+//   tile and converts all of x on each (6144 x 6144 at batch 1 8.0 us against
+//   9.8, batch 2 8.8 against 9.9; batch 3 9.7 against 10.0, batch 4 14.6
+//   against 10.2);
+// - batch 1 with more than 6144 columns, where it takes x in passes (no
+//   workspace at batch 1; 2048 x 17408 13.6 against 14.3).
+bool ks_better(int64_t B, int64_t N, int64_t K) {
+  const int64_t T = (N + 15) / 16, cus = num_cus();
+  return ks_plan(B, N, K).ok && ((B <= 2 && T > cus && T <= 2 * cus && K > 1024) || (B == 1 && K > 6144));
+}
+
 }  // namespace
 
+// (the size that callers query: what nvfp4_gemv_kernel needs; the batched
+// kernel takes no more K groups than fit in it)
 size_t gemv_nvfp4_workspace_bytes(int64_t B, int64_t N, int64_t K) {
   if (B < 1 || N == 0 || K == 0 || ks_plan(B, N, K).ok) return 0;
   return nv_plan(B, N, K).partial_bytes;
@@ -477,6 +498,10 @@ hipError_t launch_gemv_nvfp4(const uint16_t* x, int64_t B, const NvFp4View& w, i
     hipLaunchKernelGGL(nv_zero_kernel, dim3((unsigned)std::min<int64_t>(1024, (words + 255) / 256)), dim3(256), 0, s,
                        reinterpret_cast<uint32_t*>(y), words);
     return hipGetLastError();
+  }
+  if (!ks_better(B, N, K)) {
+    const hipError_t e = launch_gemv_nvfp4_batched(x, B, w, out_kind, y, ws, gemv_nvfp4_workspace_bytes(B, N, K), s);
+    if (e != hipErrorNotSupported) return e;
   }
   const KsPlan ks = ks_plan(B, N, K);
   if (ks.ok) {

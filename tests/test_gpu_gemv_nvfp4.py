@@ -1,0 +1,74 @@
+"""NVFP4A16 GEMV at the edges of its plan: rows of one scale block to 272 K
+steps (odd counts, one to three chunks per wavefront, K groups, passes over the
+activations), half row tiles, the three batch widths, both sides of the rule
+between the kernels, against the fp64 oracle element by element."""
+import ctypes
+import os
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import parity_bounds as PB  # noqa: E402
+
+import synth  # noqa: E402
+from oracle import formats, linalg, nvfp4  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+try:
+    import paper_2609_26333_amd as dq
+except ImportError:  # pragma: no cover
+    dq = None
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if dq is None or not torch.cuda.is_available():
+        pytest.skip("needs the built HIP library and a GPU")
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def check(w, xb, rows):
+    (B, K), N = xb.shape, w.shape[0]
+    Wq = dq.dq_pack_nvfp4(dev(w))
+    x = dev(xb.view(np.int16))
+    y = dq.dq_decode_gemv_nvfp4(x, Wq, out_kind=dq.OUT_F32)
+    yb = dq.dq_decode_gemv_nvfp4(x, Wq, out_kind=dq.OUT_BF16)
+    yp = torch.empty_like(y)
+    d = Wq.desc()
+    assert dq.lib().dq_decode_gemv_nvfp4(x.data_ptr(), B, ctypes.byref(d), dq.OUT_F32, yp.data_ptr(), None, 0,
+                                         torch.cuda.current_stream().cuda_stream) == dq.DQ_OK
+    torch.cuda.synchronize()
+    assert torch.equal(y, yp) and torch.equal(yb, y.bfloat16())
+    q, c, G = nvfp4.quantize_dynamic(w)
+    q, c = q[rows], c[rows]
+    bound = PB.gemv_bound(formats.f64_from_bf16_bits(xb), nvfp4.dequantize(q, c, G), K)
+    PB.assert_within(y.cpu().numpy()[:, rows], linalg.nvfp4a16_gemv(xb, q, c, G), bound, "nvfp4 gemv")
+
+
+CASES = [(5, 16, 2), (16, 48, 16), (33, 64, 5), (100, 80, 3), (47, 144, 9), (520, 512, 16), (40, 1040, 4),
+         (4096, 1040, 1), (4112, 1024, 2), (4112, 1040, 2), (4112, 1040, 3), (8192, 1088, 2), (8208, 1104, 2),
+         (8200, 1552, 8), (8200, 3088, 7), (8200, 3104, 12), (9000, 4096, 11), (250, 6144, 16), (300, 6160, 3),
+         (300, 6160, 1), (2050, 7184, 12), (70, 8208, 2), (40, 12304, 16), (2050, 17408, 6), (70, 17408, 8)]
+
+
+@pytest.mark.parametrize("N,K,B", CASES)
+def test_gemv_nvfp4(N, K, B):
+    print("nvfp4 gemv", N, K, B, flush=True)
+    w = synth.random_f32(N + K, (N, K), 0.02)
+    xb = synth.random_bf16(B + K, (B, K), outlier_frac=0.005, outlier_factor=30)
+    rows = np.arange(N) if N * K <= 1 << 20 else np.unique(np.r_[0:33, N - 20:N, np.random.default_rng(N).choice(N, 60)])
+    check(w, xb, rows)
+
+
+def test_gemv_nvfp4_scales_per_row():
+    """Batch rows of very different magnitudes: each keeps its own scale."""
+    N, K, B = 48, 4096, 16
+    x = synth.random_f32(2, (B, K)) * np.exp2(np.linspace(-60, 60, B)).astype(np.float32)[:, None]
+    check(synth.random_f32(1, (N, K), 0.02), synth.bf16_bits_from_f32(x), np.arange(N))
