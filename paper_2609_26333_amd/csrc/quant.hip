@@ -7,6 +7,7 @@
 // elements with fully coalesced 16-byte loads (8 lanes per row), computes the
 // per-16 block maxima with one cross-lane exchange, and writes the 1 KiB code
 // tile and 128-byte scale tile with contiguous stores.
+#include <algorithm>
 #include <type_traits>
 
 #include "dq_device.hpp"
@@ -109,13 +110,23 @@ __device__ inline void load8(const float* __restrict__ x, int64_t ld, int64_t ro
   }
 }
 
+// v of lane ^ 1 (quad permutation), and of lane + n within a row of 16 lanes:
+// one VALU move where __shfl takes a round trip through the LDS crossbar
+__device__ inline uint32_t lane_pair(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);
+}
+template <int n>
+__device__ inline uint32_t lane_plus(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x100 + n, 0xF, 0xF, true);   // row_shl
+}
+
 // Quantize 8 values of a 16-block whose other half lives in lane ^ 1.
 // Returns the 4 code bytes (element 2j low nibble of byte j) and the scale.
 __device__ inline uint32_t quantize8(const float (&v)[8], float G, uint32_t& scale_code) {
   float a = 0.0f;
 #pragma unroll
   for (int j = 0; j < 8; ++j) a = fmaxf(a, fabsf(v[j]));
-  a = fmaxf(a, __shfl_xor(a, 1, 64));
+  a = fmaxf(a, __uint_as_float(lane_pair(__float_as_uint(a))));
   const float den = 6.0f * G;
   const float t = a / den;                       // correctly rounded division
   const uint32_t c = e4m3_encode_rne_sat(t);
@@ -261,13 +272,20 @@ __global__ __launch_bounds__(256) void rms_rows_kernel(const uint16_t* __restric
 // wavefronts takes eight consecutive rows of one 32-row tile row, so the row
 // segments of each tile are written together.  Rows past M and columns past
 // K (tile padding) are written as zero codes and scales.
-template <int NV>
+// Bound: at many rows the fp64 sum and the exact divisions (16384 x 5120 49.9
+// us = 4.3 TB/s), at few the chain of one wavefront: NV times ~500 cycles of
+// quantization.  Few rows are therefore given to 2^WLOG wavefronts, each of
+// which holds and sums the whole row (the same value) and quantizes every
+// 2^WLOG-th vector: 168 x 5120 9.6 -> 5.7 us, 512 9.7 -> 6.6, 1024 10.0 -> 7.7.
+template <int NV, int WLOG>
 __global__ __launch_bounds__(512) void rmsnorm_quantize_rows_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ gamma, float eps, int64_t M, int64_t K,
     const float* __restrict__ Gp, uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, int64_t tiles_c,
     float* G_out) {
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t row = (int64_t)blockIdx.x * (8 >> WLOG) + (wave >> WLOG);
+  const int part = wave & ((1 << WLOG) - 1);   // quantizes the vectors of j = part, part + 2^WLOG, ..
   const float G = *Gp;
   if (blockIdx.x == 0 && threadIdx.x == 0 && G_out != nullptr) *G_out = G;
   const int nvec = (int)(K / 8), nvec_pad = (int)(tiles_c * 8);
@@ -275,10 +293,13 @@ __global__ __launch_bounds__(512) void rmsnorm_quantize_rows_kernel(
   uint4_t xr[NV];
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
-    const int v = lane + 64 * j;
-    xr[j] = uint4_t{0u, 0u, 0u, 0u};
-    if (live && v < nvec) xr[j] = *reinterpret_cast<const uint4_t*>(x + row * K + 8 * (int64_t)v);
+    const int v = min(lane + 64 * j, nvec - 1);   // (a load under a divergent branch is waited for inside it)
+    xr[j] = *reinterpret_cast<const uint4_t*>(x + min(row, M - 1) * K + 8 * (int64_t)v);
   }
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+    if (!live || 64 * j + 64 > nvec)   // uniform
+      if (!live || lane + 64 * j >= nvec) xr[j] = uint4_t{0u, 0u, 0u, 0u};
   // gamma (zero past K) into LDS once per workgroup: the eight rows share it
   __shared__ uint4_t gsh[64 * 16];
   for (int v = threadIdx.x; v < nvec_pad; v += 512)
@@ -301,14 +322,21 @@ __global__ __launch_bounds__(512) void rmsnorm_quantize_rows_kernel(
     const float r = ms + eps;
     iv = 1.0f / sqrtf(r);
   }
+  // (the row is unpacked again below: kept as fp32 from here it would take
+  // twice the registers)
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) asm("" : "+v"(xr[j][t]));
   __syncthreads();
   const int64_t tr = row / 32, rr = row % 32;
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const int v = lane + 64 * j;
-    if (64 * j >= nvec_pad) break;            // uniform: no vector of this j in the padded row
+    if ((j & ((1 << WLOG) - 1)) != part) continue;   // uniform
+    __builtin_amdgcn_sched_barrier(0);   // one vector's temporaries at a time (registers)
     float f[8];
-    const uint4_t gw = v < nvec_pad ? gsh[v] : uint4_t{0u, 0u, 0u, 0u};
+    const uint4_t gw = gsh[v];   // (of the last j, past the padded row: not stored)
 #pragma unroll
     for (int t = 0; t < 4; ++t) {     // two roundings, in this order (zeros stay zero)
       f[2 * t] = (bf16_lo(xr[j][t]) * iv) * bf16_lo(gw[t]);
@@ -317,10 +345,8 @@ __global__ __launch_bounds__(512) void rmsnorm_quantize_rows_kernel(
     uint32_t sc;
     const uint32_t w = quantize8(f, G, sc);   // every lane takes part in the pair exchange
     // the scales of the tile row's four 16-blocks, gathered in the lane with v % 8 == 0
-    const uint32_t s2 = (uint32_t)__shfl((int)sc, lane + 2, 64);
-    const uint32_t s4 = (uint32_t)__shfl((int)sc, lane + 4, 64);
-    const uint32_t s6 = (uint32_t)__shfl((int)sc, lane + 6, 64);
-    if (v < nvec_pad) {
+    const uint32_t s2 = lane_plus<2>(sc), s4 = lane_plus<4>(sc), s6 = lane_plus<6>(sc);
+    if (j + 1 < NV || v < nvec_pad) {
       const int64_t tile = tr * tiles_c + v / 8;
       *reinterpret_cast<uint32_t*>(codes + tile * 1024 + rr * 32 + 4 * (v % 8)) = w;
       if ((v & 7) == 0)
@@ -388,15 +414,18 @@ hipError_t launch_rmsnorm_quantize_act(const uint16_t* X, const uint16_t* gamma,
     const int nv = (int)((tiles_c * 8 + 63) / 64);
     typedef void (*kern_t)(const uint16_t*, const uint16_t*, float, int64_t, int64_t, const float*, uint8_t*,
                            uint8_t*, int64_t, float*);
-    static const kern_t kerns[16] = {
-        rmsnorm_quantize_rows_kernel<1>,  rmsnorm_quantize_rows_kernel<2>,  rmsnorm_quantize_rows_kernel<3>,
-        rmsnorm_quantize_rows_kernel<4>,  rmsnorm_quantize_rows_kernel<5>,  rmsnorm_quantize_rows_kernel<6>,
-        rmsnorm_quantize_rows_kernel<7>,  rmsnorm_quantize_rows_kernel<8>,  rmsnorm_quantize_rows_kernel<9>,
-        rmsnorm_quantize_rows_kernel<10>, rmsnorm_quantize_rows_kernel<11>, rmsnorm_quantize_rows_kernel<12>,
-        rmsnorm_quantize_rows_kernel<13>, rmsnorm_quantize_rows_kernel<14>, rmsnorm_quantize_rows_kernel<15>,
-        rmsnorm_quantize_rows_kernel<16>};
-    hipLaunchKernelGGL(kerns[nv - 1], dim3((unsigned)(tiles_r * 4)), dim3(512), 0, s, X, gamma, eps, M, K, G_static,
-                       out.codes, out.scales, tiles_c, G_static == out.G ? nullptr : out.G);
+#define ROWS(NV) {rmsnorm_quantize_rows_kernel<NV, 0>, rmsnorm_quantize_rows_kernel<NV, 1>, \
+                  rmsnorm_quantize_rows_kernel<NV, 2>, rmsnorm_quantize_rows_kernel<NV, 3>}
+    static const kern_t kerns[16][4] = {ROWS(1),  ROWS(2),  ROWS(3),  ROWS(4),  ROWS(5),  ROWS(6),  ROWS(7),  ROWS(8),
+                                        ROWS(9),  ROWS(10), ROWS(11), ROWS(12), ROWS(13), ROWS(14), ROWS(15), ROWS(16)};
+#undef ROWS
+    // wavefronts per row while the rows alone leave the chip idle (K = 5120,
+    // 1 / 2 / 4 / 8 of them: 256 rows 9.4 / 7.0 / 6.3 / 5.7 us, 512 9.6 / 7.4 /
+    // 6.7 / 8.1, 1024 9.9 / 7.8 / 9.4 / 12.5, 1536 10.4 / 10.8), at most NV
+    const int by_rows = M <= 256 ? 3 : M <= 512 ? 2 : M <= 1024 ? 1 : 0;
+    const int wlog = std::min(by_rows, nv >= 8 ? 3 : nv >= 4 ? 2 : nv >= 2 ? 1 : 0);
+    hipLaunchKernelGGL(kerns[nv - 1][wlog], dim3((unsigned)(tiles_r * 4 << wlog)), dim3(512), 0, s, X, gamma, eps, M, K,
+                       G_static, out.codes, out.scales, tiles_c, G_static == out.G ? nullptr : out.G);
     return hipGetLastError();
   }
   float* inv = reinterpret_cast<float*>(ws);
