@@ -128,9 +128,9 @@ __device__ inline void store_group(uint8_t* codes, int64_t row, int64_t group, i
 // Bound: the VALU (about 78 instructions per value) and the LDS accesses
 // beside it; the row is read once.  A bitonic sort of the row in LDS (78
 // passes at K = 4096) took 1417 us for 12288 x 4096, this takes 157
-// (1.4 TB/s; 475 with weights of few distinct values).  Thresholds by comparison for every value, four wavefronts per row instead
-// of two and a full double-double merge took 207.  The 16 rows of a tile run
-// on one XCD, so that their 12-byte groups merge into whole lines in its L2.
+// (1.4 TB/s; 475 with weights of few distinct values).  Thresholds by
+// comparison for every value, four wavefronts per row instead of two and a
+// full double-double merge took 207.  The 16 rows of a tile run on one XCD, so that their 12-byte groups merge into whole lines in its L2.
 constexpr int kBuckets = 2048;
 constexpr int kCap = 128;   // members of a threshold's bucket that are listed and ranked
 
