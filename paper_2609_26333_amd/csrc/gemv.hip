@@ -32,6 +32,7 @@
 #include "dq.h"
 #include "dq_device.hpp"
 #include "dq_internal.hpp"
+#include "gemv_plan.hpp"
 
 namespace dq {
 
@@ -711,14 +712,7 @@ constexpr int kRingMulti = 8;
 // the code stream (34816 x 5120, 100 MB: 24.2 us = 4.1 TB/s).  Against K
 // slices of x staged in LDS and a reduction launch: 27B block at batch 4 73.8
 // -> 63.6 us, 16 107 -> 84; 12288 x 4096 at batch 4 13.1 -> 9.1.
-struct BatchPlan {
-  int KG, KCR, TPG;   // K groups, chunks per K group, tiles per workgroup
-  int tiles, KC;
-  int KT;             // NVFP4: K steps of 64 columns
-};
 typedef uint16_t ushort2_t __attribute__((ext_vector_type(2)));
-constexpr int kAhead = 2;   // tiles of codes in flight per wavefront
-constexpr int kParkBytes = 144 * 1024;
 
 // dword of the lane n places further on in its row of 16 (cyclically)
 template <int n>
@@ -751,7 +745,6 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
   const bool xlane = j < B;
   constexpr int NV = BV / 4;      // 16-byte loads per lane and chunk
   const int jx = j % BV;          // the batch row this lane loads for
-  constexpr int32_t kNowhere = 0x7FFFFFFF;   // an offset past every buffer: the load returns zero and reads nothing
 
   const i32x4_t rx = buffer_resource(x, (uint32_t)((int64_t)B * K * 2));
   // ---- 2. tables and codes of the first tiles (past the last tile, and past
@@ -771,33 +764,36 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
   int cp = c0, nu = 0;   // this pass: first chunk, chunks of this wavefront (<= CPW)
   auto load_chunk = [&](int t, int r, int u) {
     const bool ok = t < nt && u < nu;
-    const int cidx = (t0 + t) * KC + cp + u * W + wave;   // (out of range: not read, whatever it is)
-    const int32_t vc = ok ? lane_code : kNowhere - 64;
+    const int c = cp + u * W + wave;
     if constexpr (MODE == 2) {
-      const int st0 = 2 * (cp + u * W + wave), half = (t0 + t) & 1;
-      const int step = (((t0 + t) >> 1) - p0) * plan.KT + st0;
+      const int pair = ((t0 + t) >> 1) - p0, half = (t0 + t) & 1;
+      const int32_t at = nvfp4_chunk_at(ok, pair, plan.KT, c, half);
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const bool in = ok && st0 + h < plan.KT;
-        const i32x2_t v = raw_buffer_load_b64(rcodes, in ? lane_code : kNowhere - 64, (step + h) * 1024 + half * 512, 0);
+        const LoadAt a = nvfp4_step_at(ok, at, 2 * c + h, plan.KT, h, lane_code, 4 * i);
+        const i32x2_t v = raw_buffer_load_b64(rcodes, a.lane, a.uniform, 0);
         ring[r][u].w[2 * h] = (uint32_t)v[0];
         ring[r][u].w[2 * h + 1] = (uint32_t)v[1];
-        sring[r][u][h] =
-            (uint32_t)raw_buffer_load_b32(rscales, in ? 4 * i : kNowhere - 64, (step + h) * 128 + half * 64, 0);
+        sring[r][u][h] = (uint32_t)raw_buffer_load_b32(rscales, a.lane_scale, a.uniform / 8, 0);
       }
-    } else if constexpr (BITS == 3) {
-      const i32x3_t v = raw_buffer_load_b96(rcodes, vc, cidx * kChunkBytes, 0);
-      ring[r][u] = cvec{{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2]}};
     } else {
-      const i32x2_t v = raw_buffer_load_b64(rcodes, vc, cidx * kChunkBytes, 0);
-      ring[r][u] = cvec{{(uint32_t)v[0], (uint32_t)v[1]}};
+      const LoadAt ac = lut_chunk_at(ok, t0 + t, KC, c, kChunkBytes, lane_code);
+      if constexpr (BITS == 3) {
+        const i32x3_t v = raw_buffer_load_b96(rcodes, ac.lane, ac.uniform, 0);
+        ring[r][u] = cvec{{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2]}};
+      } else {
+        const i32x2_t v = raw_buffer_load_b64(rcodes, ac.lane, ac.uniform, 0);
+        ring[r][u] = cvec{{(uint32_t)v[0], (uint32_t)v[1]}};
+      }
     }
-    if (MODE == 1)
-      sring[r][u][0] = (uint32_t)raw_buffer_load_b32(rscales, ok ? lane_scale & ~3 : kNowhere - 64, cidx * 128, 0);
+    if (MODE == 1) {
+      const LoadAt as = lut_chunk_at(ok, t0 + t, KC, c, 128, lane_scale & ~3);
+      sring[r][u][0] = (uint32_t)raw_buffer_load_b32(rscales, as.lane, as.uniform, 0);
+    }
   };
   auto load_tab = [&](int t, int r) {
     if constexpr (MODE != 0) return;
-    const int32_t off = t < nt ? (t0 + t) * kTabBytes + lane_tab : kNowhere - 64;
+    const int32_t off = t < nt ? (t0 + t) * kTabBytes + lane_tab : kNowhere;
     if constexpr (BITS == 3) {
       const i32x4_t v = raw_buffer_load_b128(rtab, off, 0, 0);
       tab[r] = uint4_t{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
@@ -819,12 +815,12 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
       const int64_t k = (int64_t)(cp + u * W + wave) * 128 + (MODE == 2 ? 16 : 32) * q;
       const bool in = u < nu && jx < B && k < K, in2 = MODE == 2 ? u < nu && jx < B && k + 64 < K : in;
       const int32_t base = (int32_t)((jx * K + k) * 2);
-      const int32_t off_lut = in ? base + j / BV * (NV * 16) : kNowhere - 64;
+      const int32_t off_lut = in ? base + j / BV * (NV * 16) : kNowhere;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         const int vv = j / BV * NV + v;   // NVFP4: 16-byte piece of the lane's columns
         const int32_t off = MODE != 2 ? off_lut + 16 * v
-                                      : (vv >> 1 ? in2 : in) ? base + 128 * (vv >> 1) + 16 * (vv & 1) : kNowhere - 64;
+                                      : (vv >> 1 ? in2 : in) ? base + 128 * (vv >> 1) + 16 * (vv & 1) : kNowhere;
         const i32x4_t w = raw_buffer_load_b128(rx, off, 0, 0);
         xr[u][v] = uint4_t{(uint32_t)w[0], (uint32_t)w[1], (uint32_t)w[2], (uint32_t)w[3]};
       }
@@ -1167,67 +1163,6 @@ inline int persist_wgs_per_cu(int vgprs, int waves, int64_t lds) {
   return std::max(1, std::min(by_vgpr, by_lds));
 }
 
-// K groups whose partial sums the workspace of a batch B >= 2 call holds (the
-// size that callers query, and the limit of the no-allocation variant): the
-// plan below uses at most these.
-inline int64_t contract_groups(int64_t B, int64_t T, int64_t KC) {
-  const int64_t tasks = (int64_t)num_cus() * (B >= 12 ? 6 : 12);
-  const int64_t by_slice = std::max<int64_t>(1, (40 * 1024) / (B * 256));
-  const int64_t KG = std::max<int64_t>((KC + by_slice - 1) / by_slice, std::min<int64_t>(KC, (tasks + T - 1) / T));
-  const int64_t KCR = (KC + KG - 1) / KG;
-  return (KC + KCR - 1) / KCR;
-}
-
-// Plan of the batch B >= 2 kernel (see lut_gemv_batch_kernel), with at most
-// `most` K groups.
-struct BatchedPlan {
-  bool ok;                   // false: the matrix exceeds the kernel's 32-bit offsets
-  int64_t W, CPW;            // wavefronts per workgroup, chunks per wavefront and pass
-  int64_t KG, KCR, TPG, G;   // K groups, chunks per group, tiles per workgroup, workgroups
-  int64_t park;              // tiles parked in LDS
-};
-
-inline bool batched_ok(int bits, int64_t T, int64_t KC) {
-  if (bits == 4) return KC * 2048 * 4 < ((int64_t)1 << 31);   // (offsets within a workgroup's tiles only)
-  return T * KC * 64 * (bits == 3 ? 12 : 8) < ((int64_t)1 << 31);
-}
-
-inline BatchedPlan plan_batched(int bits, int64_t B, int64_t T, int64_t KC, int64_t most) {
-  BatchedPlan p{};
-  p.ok = batched_ok(bits, T, KC) && B * KC * 256 < ((int64_t)1 << 31);
-  // sixteen wavefronts of at most three chunks (48 activation registers, of
-  // the 128 that leave four wavefronts per SIMD).  Short rows take fewer
-  // wavefronts and as many more workgroups per compute unit: with several
-  // tiles per workgroup as few as hold the row (two or three chunks share a
-  // tile's set-up: 65536 x 1056 at batch 2 14.7 -> 9.9 us), else one chunk
-  // each.  More than 48 chunks: K groups, or passes where the workspace holds
-  // too few groups.
-  const int64_t cus = num_cus();
-  const bool deep = T >= 2 * cus;
-  p.W = deep ? (KC > 24 ? 16 : KC > 12 ? 8 : 4) : (KC > 8 ? 16 : KC > 4 ? 8 : 4);
-  const int64_t fit = 3 * p.W;
-  p.KG = std::min((KC + fit - 1) / fit, most);
-  // few tiles: more K groups use the idle compute units and leave each less of
-  // x to convert, which pays for the reduction pass where there is one anyway
-  // or the batch is large (batch 16: 512 x 12288 11.9 -> 8.2 us, 2048 x 6144
-  // 10.1 -> 9.5)
-  if (T * p.KG <= cus && (p.KG > 1 || (B > 8 && KC > 40)))
-    p.KG = std::min(most, std::max(p.KG, std::min((KC + p.W - 1) / p.W, (B > 8 ? 2 : 1) * cus / T)));
-  p.KCR = (KC + p.KG - 1) / p.KG;
-  p.KG = (KC + p.KCR - 1) / p.KCR;
-  const int64_t passes = (p.KCR + fit - 1) / fit;
-  p.CPW = (p.KCR + passes * p.W - 1) / (passes * p.W);
-  const int64_t slots = cus * (16 / p.W), fits = kParkBytes / (16 * 1024);   // W KiB a tile, 16 / W workgroups
-  int64_t groups = std::min<int64_t>(T, std::max<int64_t>(1, slots / p.KG));
-  if (passes > 1)   // every tile stays parked over the passes: whole rounds of fuller workgroups
-    groups *= (T + groups * fits - 1) / (groups * fits);
-  p.TPG = (T + groups - 1) / groups;
-  if (bits == 4) p.TPG = std::min(p.TPG, (((int64_t)1 << 31) - 4096) / (KC * 1024) - 2);
-  p.G = (T + p.TPG - 1) / p.TPG * p.KG;
-  p.park = std::min<int64_t>(p.TPG, fits);
-  return p;
-}
-
 // Batch B >= 2: the batched kernel, and with more than one K group a reduction
 // pass over the K-group partials, held in the caller's workspace `ws` (at
 // least gemv_workspace_bytes) or, when ws is NULL, in stream-ordered staging
@@ -1237,7 +1172,7 @@ template <int BITS, int MODE>
 hipError_t launch_gemv_batched(const uint16_t* x, int64_t B, const LutView& w, int out_kind, void* y, void* ws,
                                hipStream_t s, int64_t T, int64_t KC, int64_t most) {
   const int64_t N = w.rows, K = w.cols;
-  const BatchedPlan p = plan_batched(BITS, B, T, KC, most);
+  const BatchedPlan p = plan_batched(BITS, B, T, KC, most, num_cus());
   if (!p.ok) return hipErrorNotSupported;
   typedef void (*kern_t)(const uint16_t*, int64_t, int, const uint8_t*, const uint16_t*, const uint8_t*,
                          const float*, int64_t, BatchPlan, int, float*, int, void*);
@@ -1288,7 +1223,7 @@ hipError_t launch_gemv_t(const uint16_t* x, int64_t B, const LutView& w, int out
   pl.KC = round_up(K, 128) / 128;
   if (B >= 2) {
     const hipError_t e = launch_gemv_batched<BITS, MODE>(x, B, w, out_kind, y, ws, s, pl.tiles, pl.KC,
-                                                           contract_groups(B, pl.tiles, pl.KC));
+                                                           contract_groups(B, pl.tiles, pl.KC, num_cus()));
     if (e != hipErrorNotSupported) return e;
   }
   // Persistent kernel whenever the staged activations leave room for at
@@ -1426,7 +1361,7 @@ hipError_t gemv_noalloc_scratch(void** ptr) {
 size_t gemv_workspace_bytes(int64_t B, const LutView& w) {
   if (B < 2 || w.rows == 0 || w.cols == 0) return 0;
   const int64_t T = round_up(w.rows, 16) / 16, KC = round_up(w.cols, 128) / 128;
-  const int64_t KG = batched_ok(w.bits, T, KC) ? contract_groups(B, T, KC) : 1;
+  const int64_t KG = batched_ok(w.bits, T, KC) ? contract_groups(B, T, KC, num_cus()) : 1;
   return KG > 1 ? (size_t)(KG * T * B * 16 * 4) : 0;
 }
 

@@ -35,7 +35,8 @@
 namespace dq {
 
 // Raw buffer loads (LLVM AMDGPU intrinsics): a scalar resource, a per-lane
-// offset and a uniform offset; offsets past the resource size read zero.
+// offset and a uniform offset; a lane offset past what the uniform offset
+// leaves of the resource reads zero.
 typedef int32_t v4i_t __attribute__((ext_vector_type(4)));
 __device__ v4i_t nv_buffer_load_b128(v4i_t rsrc, int32_t voff, int32_t soff,
                                      int32_t aux) __asm("llvm.amdgcn.raw.buffer.load.v4i32");
@@ -122,9 +123,10 @@ __global__ __launch_bounds__(256) void nvfp4_gemv_kernel(const uint16_t* __restr
     const v4i_t rs = nv_resource(scales + ((int64_t)(ok ? t : 0) * KT + kt0) * 128, ok ? (uint32_t)valid * 128u : 0u);
 #pragma unroll
     for (int u = 0; u < kCyc; ++u) {
-      const v4i_t v = nv_buffer_load_b128(rc, c_off, (st0 + u) * 1024, 0);
+      const int st = min(st0 + u, ok ? valid : 0);   // (the uniform offset stays within the resource)
+      const v4i_t v = nv_buffer_load_b128(rc, c_off, st * 1024, 0);
       cb.c[u] = uint4_t{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
-      cb.s[u] = (uint16_t)nv_buffer_load_b16(rs, s_off, (st0 + u) * 128, 0);
+      cb.s[u] = (uint16_t)nv_buffer_load_b16(rs, s_off, st * 128, 0);
     }
   };
   issue(0, cb0);
@@ -298,9 +300,10 @@ __global__ __launch_bounds__(64 * kKsWaves) void nvfp4_gemv_ks_kernel(
   auto issue = [&](int q, Cycle& cb) {
 #pragma unroll
     for (int u = 0; u < kCyc; ++u) {
-      const v4i_t v = nv_buffer_load_b128(rc, c_off, (kCyc * q + u) * 1024, 0);
+      const int st = min(kCyc * q + u, nst);   // (the uniform offset stays within the resource)
+      const v4i_t v = nv_buffer_load_b128(rc, c_off, st * 1024, 0);
       cb.c[u] = uint4_t{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
-      cb.s[u] = (uint16_t)nv_buffer_load_b16(rs, s_off, (kCyc * q + u) * 128, 0);
+      cb.s[u] = (uint16_t)nv_buffer_load_b16(rs, s_off, st * 128, 0);
     }
   };
   __builtin_amdgcn_sched_barrier(0);
