@@ -409,9 +409,10 @@ __global__ __launch_bounds__(256) void nvfp4_gemv_reduce_kernel(const float* __r
   }
 }
 
-__global__ void nv_zero_kernel(uint32_t* __restrict__ p, int64_t words) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < words; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0u;
+// n zero elements of 4 (fp32) or 2 (bf16) bytes
+template <typename T>
+__global__ void nv_zero_kernel(T* __restrict__ p, int64_t n) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0;
 }
 
 struct NvGemvPlan {
@@ -497,9 +498,12 @@ hipError_t launch_gemv_nvfp4(const uint16_t* x, int64_t B, const NvFp4View& w, i
   const int64_t N = w.rows, K = w.cols;
   if (N == 0 || B == 0) return hipSuccess;
   if (K == 0) {   // empty sum: y = 0 (fp32 or bf16 zeros are all-zero bits)
-    const int64_t words = (B * N * (out_kind == 0 ? 4 : 2) + 3) / 4;
-    hipLaunchKernelGGL(nv_zero_kernel, dim3((unsigned)std::min<int64_t>(1024, (words + 255) / 256)), dim3(256), 0, s,
-                       reinterpret_cast<uint32_t*>(y), words);
+    const int64_t n = B * N;
+    const dim3 grid((unsigned)std::min<int64_t>(1024, (n + 255) / 256));
+    if (out_kind == 0)
+      hipLaunchKernelGGL(nv_zero_kernel<uint32_t>, grid, dim3(256), 0, s, reinterpret_cast<uint32_t*>(y), n);
+    else
+      hipLaunchKernelGGL(nv_zero_kernel<uint16_t>, grid, dim3(256), 0, s, reinterpret_cast<uint16_t*>(y), n);
     return hipGetLastError();
   }
   if (!ks_better(B, N, K)) {

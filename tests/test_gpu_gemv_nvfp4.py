@@ -72,3 +72,15 @@ def test_gemv_nvfp4_scales_per_row():
     N, K, B = 48, 4096, 16
     x = synth.random_f32(2, (B, K)) * np.exp2(np.linspace(-60, 60, B)).astype(np.float32)[:, None]
     check(synth.random_f32(1, (N, K), 0.02), synth.bf16_bits_from_f32(x), np.arange(N))
+
+
+@pytest.mark.parametrize("out_kind,dtype", [(dq.OUT_F32, torch.float32), (dq.OUT_BF16, torch.bfloat16)] if dq else [])
+@pytest.mark.parametrize("N,B", [(5, 3), (1, 1), (300, 7)])
+def test_gemv_nvfp4_no_columns(N, B, out_kind, dtype):
+    """K = 0: zeros in y and nothing behind it (odd element counts)."""
+    Wq = dq.NvFp4Tensor.empty(N, 0)
+    x = torch.empty((B, 0), dtype=torch.bfloat16, device="cuda")
+    buf = torch.full((B * N + 8,), 7.0, dtype=dtype, device="cuda")
+    dq.dq_decode_gemv_nvfp4(x, Wq, out_kind=out_kind, y=buf[:B * N].view(B, N))
+    torch.cuda.synchronize()
+    assert not buf[:B * N].any() and (buf[B * N:] == 7.0).all()
