@@ -777,18 +777,15 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
         sring[r][u][h] = (uint32_t)raw_buffer_load_b32(rscales, a.lane_scale, a.uniform / 8, 0);
       }
     } else {
-      const LoadAt ac = lut_chunk_at(ok, t0 + t, KC, c, kChunkBytes, lane_code);
+      const LoadAt a = lut_chunk_at(ok, t0 + t, KC, c, lane_code, lane_scale & ~3);
       if constexpr (BITS == 3) {
-        const i32x3_t v = raw_buffer_load_b96(rcodes, ac.lane, ac.uniform, 0);
+        const i32x3_t v = raw_buffer_load_b96(rcodes, a.lane, a.uniform * kChunkBytes, 0);
         ring[r][u] = cvec{{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2]}};
       } else {
-        const i32x2_t v = raw_buffer_load_b64(rcodes, ac.lane, ac.uniform, 0);
+        const i32x2_t v = raw_buffer_load_b64(rcodes, a.lane, a.uniform * kChunkBytes, 0);
         ring[r][u] = cvec{{(uint32_t)v[0], (uint32_t)v[1]}};
       }
-    }
-    if (MODE == 1) {
-      const LoadAt as = lut_chunk_at(ok, t0 + t, KC, c, 128, lane_scale & ~3);
-      sring[r][u][0] = (uint32_t)raw_buffer_load_b32(rscales, as.lane, as.uniform, 0);
+      if (MODE == 1) sring[r][u][0] = (uint32_t)raw_buffer_load_b32(rscales, a.lane_scale, a.uniform * 128, 0);
     }
   };
   auto load_tab = [&](int t, int r) {

@@ -32,11 +32,11 @@ constexpr int kParkBytes = 144 * 1024;
 constexpr int32_t kNowhere = 0x7FFFFFFF - 64;
 struct LoadAt {
   int32_t lane, uniform;
-  int32_t lane_scale;   // NVFP4: of the block scales, at uniform / 8
+  int32_t lane_scale;   // of the block scales of the same chunk or K step
 };
-// LUT: `bytes` of codes or block scales a chunk, chunks tile by tile
-DQ_HOST_DEVICE inline LoadAt lut_chunk_at(bool wanted, int tile, int KC, int chunk, int bytes, int32_t lane) {
-  return LoadAt{wanted ? lane : kNowhere, wanted ? (tile * KC + chunk) * bytes : 0, 0};
+// LUT: `uniform` in chunks from the start of the matrix
+DQ_HOST_DEVICE inline LoadAt lut_chunk_at(bool wanted, int tile, int KC, int chunk, int32_t lane, int32_t lane_scale) {
+  return LoadAt{wanted ? lane : kNowhere, wanted ? tile * KC + chunk : 0, wanted ? lane_scale : kNowhere};
 }
 // NVFP4: a chunk's first K step in half of the 32-row tile `pair`, in bytes of
 // codes from the start of the buffer
@@ -44,6 +44,7 @@ DQ_HOST_DEVICE inline int32_t nvfp4_chunk_at(bool wanted, int pair, int KT, int 
   return wanted ? (pair * KT + 2 * chunk) * 1024 + half * 512 : 0;
 }
 // and its K step `step` (h = 0 or 1), which the last chunk of an odd KT lacks
+// (the scales at `uniform` / 8)
 DQ_HOST_DEVICE inline LoadAt nvfp4_step_at(bool wanted, int32_t chunk_at, int step, int KT, int h, int32_t lane,
                                            int32_t lane_scale) {
   const bool in = h == 0 ? wanted : wanted && step < KT;

@@ -54,7 +54,8 @@ int64_t gemv_bad_loads(int bits, int64_t B, int64_t T, int64_t KC, int64_t KT, i
                 a = dq::nvfp4_step_at(ok, dq::nvfp4_chunk_at(ok, pair, (int)KT, c, half), 2 * c + h, (int)KT, h, lane, lane);
                 if (scales) a = dq::LoadAt{a.lane_scale, a.uniform / 8, 0};
               } else {
-                a = dq::lut_chunk_at(want, t0 + t, (int)KC, c, chunk_bytes, lane);
+                a = dq::lut_chunk_at(want, t0 + t, (int)KC, c, lane, lane);
+                a = dq::LoadAt{scales ? a.lane_scale : a.lane, a.uniform * chunk_bytes, 0};
               }
               const int64_t l = (uint32_t)a.lane, s = (uint32_t)a.uniform;
               if (s > records || l + s >= ((int64_t)1 << 32)) ++bad;
