@@ -684,19 +684,23 @@ constexpr int kRingMulti = 8;
 // ---------------------------------------------------------------- batched
 // Batch B >= 2: the activations live in registers.  A workgroup of up to
 // sixteen wavefronts (one workgroup of sixteen per compute unit) takes K group
-// kg (KCR chunks; one group up to 6144 columns) of a run of row tiles; its
-// wavefront w owns chunks w, w + W, .. (at most CPW) of the group for the
-// whole run (or one pass over it) and holds their activations as MFMA operands: lane (q, j) has
+// kg (KCR chunks; see plan_batched) of a run of row tiles; its wavefront w
+// owns chunks w, w + W, .. (at most CPW) of the group for the whole run (or
+// one pass over it) and holds their activations as MFMA operands: lane (q, j) has
 // columns 32q .. 32q + 31 of batch row j of each chunk, 16 registers a chunk,
 // loaded straight from x, rescaled by a power of two from the largest
 // magnitude of the lane's row in the wavefront's chunks (exact for every value
 // within 2^31 of it) and converted to fp16 in place.  Nothing is staged in LDS
 // and nothing is shared before the reduction.  The code stream runs kAhead
-// tiles ahead.  Each wavefront parks its unscaled 16 x 16 partial tile in LDS;
-// after one barrier per kPark tiles, wavefront r adds the W partials of tile r
+// tiles ahead.  Each wavefront parks the batch columns of its unscaled 16 x 16
+// partial tile in LDS (up to 9, 18 or 36 tiles at 16, 8 or 4 columns);
+// after one barrier per `park` tiles, wavefront r adds the W partials of tile r
 // in wavefront order and stores the tile (to y, or with more than one K group
 // to the partial sums that a second pass adds in K-group order): results are
-// deterministic.
+// deterministic.  With passes every tile stays parked until the last one, so
+// parking only the columns that are used (all sixteen lanes' before) lets a
+// compute unit convert x once: LUT3 65536 x 17408 at batch 2 108 -> 95 us,
+// 49168 x 8192 43.6 -> 36.5.
 // Bound: VALU issue of the lookups (about 54 instructions per 2048-code chunk)
 // with the code stream beside it, and at the small matrices the launch, one
 // memory round trip and the conversion (350 instructions a wavefront at three
@@ -733,7 +737,8 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
   constexpr int kChunkBytes = 64 * CodeVec<BITS>::bytes;
   constexpr int kTabBytes = 16 * 2 * (1 << BITS);
   extern __shared__ __align__(16) uint8_t smem[];
-  float4_t* part = reinterpret_cast<float4_t*>(smem);   // [park][W][64]
+  constexpr int kSlot = 4 * BV;                         // lanes of a parked partial tile: (q, j < BV)
+  float4_t* part = reinterpret_cast<float4_t*>(smem);   // [park][W][kSlot]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int W = blockDim.x >> 6;
@@ -745,9 +750,10 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
   const bool xlane = j < B;
   constexpr int NV = BV / 4;      // 16-byte loads per lane and chunk
   const int jx = j % BV;          // the batch row this lane loads for
+  const int lane_slot = BV == 16 ? lane : q * BV + jx;
 
   const i32x4_t rx = buffer_resource(x, (uint32_t)((int64_t)B * K * 2));
-  // ---- 2. tables and codes of the first tiles (past the last tile, and past
+  // ---- 1. tables and codes of the first tiles (past the last tile, and past
   // the wavefront's last chunk: nothing is read)
   // (NVFP4: tiles of 32 rows x 64 columns, addressed from the workgroup's first)
   const int p0 = t0 >> 1, np = ((t0 + nt + 1) >> 1) - p0;
@@ -801,7 +807,7 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
   };
   uint4_t xr[CPW][4];
   float unscale = 1.0f;
-  // ---- 3. a pass's activations (64 bytes per lane and chunk), with the codes
+  // ---- 2. a pass's activations (64 bytes per lane and chunk), with the codes
   // of its first tiles behind them; rescaled and converted (see the batch-1
   // kernel: exact, or an fp16 subnormal more than 2^31 below the maximum)
   auto load_pass = [&]() __attribute__((always_inline)) {
@@ -865,7 +871,7 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
         }
   };
 
-  // ---- 4. tiles
+  // ---- 3. tiles
   uint32_t tl0, tl1, th0, th1;
   if (MODE == 1) table_pools<BITS>(load_table<BITS>(lut), tl0, tl1, th0, th1);
   int parked = 0;   // tiles in LDS
@@ -917,13 +923,15 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
     float4_t sum;
 #pragma unroll
     for (int r2 = 0; r2 < 4; ++r2) sum[r2] = acc[r2] * unscale;
-    float4_t* slot = part + (parked * W + wave) * 64 + lane;
-    if (!first) {
-      const float4_t o = *slot;
+    if (BV == 16 || j < BV) {   // (the other lanes' columns are nobody's)
+      float4_t* slot = part + (parked * W + wave) * kSlot + lane_slot;
+      if (!first) {
+        const float4_t o = *slot;
 #pragma unroll
-      for (int r2 = 0; r2 < 4; ++r2) sum[r2] += o[r2];
+        for (int r2 = 0; r2 < 4; ++r2) sum[r2] += o[r2];
+      }
+      *slot = sum;
     }
-    *slot = sum;
     if (++parked == park || t + 1 == nt) {   // uniform over the workgroup
       if (!last) {   // more passes: every tile of the workgroup is parked
         parked = 0;
@@ -931,11 +939,11 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
       }
       __syncthreads();
       for (int p = wave; p < parked; p += W) {
-        const float4_t* pr = part + (size_t)p * W * 64 + lane;
+        const float4_t* pr = part + p * W * kSlot + lane_slot;
         float4_t o = pr[0];
 #pragma unroll 4
         for (int w2 = 1; w2 < W; ++w2) {
-          const float4_t t2 = pr[w2 * 64];
+          const float4_t t2 = pr[w2 * kSlot];
 #pragma unroll
           for (int r2 = 0; r2 < 4; ++r2) o[r2] += t2[r2];
         }
@@ -1177,8 +1185,8 @@ hipError_t launch_gemv_batched(const uint16_t* x, int64_t B, const LutView& w, i
       {lut_gemv_batch_kernel<BITS, MODE, 1, 4>, lut_gemv_batch_kernel<BITS, MODE, 1, 8>, lut_gemv_batch_kernel<BITS, MODE, 1, 16>},
       {lut_gemv_batch_kernel<BITS, MODE, 2, 4>, lut_gemv_batch_kernel<BITS, MODE, 2, 8>, lut_gemv_batch_kernel<BITS, MODE, 2, 16>},
       {lut_gemv_batch_kernel<BITS, MODE, 3, 4>, lut_gemv_batch_kernel<BITS, MODE, 3, 8>, lut_gemv_batch_kernel<BITS, MODE, 3, 16>}};
-  const kern_t kern = kerns[p.CPW - 1][B > 8 ? 2 : B > 4 ? 1 : 0];
-  const size_t lds = (size_t)(p.park * p.W * 1024);
+  const kern_t kern = kerns[p.CPW - 1][p.BV == 16 ? 2 : p.BV == 8 ? 1 : 0];
+  const size_t lds = (size_t)(p.park * p.W * p.BV * 64);
   float* partials = reinterpret_cast<float*>(ws);
   const bool pooled = p.KG > 1 && partials == nullptr;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,

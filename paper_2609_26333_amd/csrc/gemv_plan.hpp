@@ -66,6 +66,7 @@ inline int64_t contract_groups(int64_t B, int64_t T, int64_t KC, int64_t cus) {
 // `most` K groups.
 struct BatchedPlan {
   bool ok;                   // false: the matrix exceeds the kernel's 32-bit offsets
+  int64_t BV;                // batch columns of the kernel (4, 8 or 16 >= B)
   int64_t W, CPW;            // wavefronts per workgroup, chunks per wavefront and pass
   int64_t KG, KCR, TPG, G;   // K groups, chunks per group, tiles per workgroup, workgroups
   int64_t park;              // tiles parked in LDS
@@ -84,23 +85,46 @@ inline BatchedPlan plan_batched(int bits, int64_t B, int64_t T, int64_t KC, int6
   // wavefronts and as many more workgroups per compute unit: with several
   // tiles per workgroup as few as hold the row (two or three chunks share a
   // tile's set-up: 65536 x 1056 at batch 2 14.7 -> 9.9 us), else one chunk
-  // each.  More than 48 chunks: K groups, or passes where the workspace holds
-  // too few groups.
+  // each.  More than 48 chunks: K groups, or passes over the parked tiles.
+  p.BV = B > 8 ? 16 : B > 4 ? 8 : 4;
   const bool deep = T >= 2 * cus;
   p.W = deep ? (KC > 24 ? 16 : KC > 12 ? 8 : 4) : (KC > 8 ? 16 : KC > 4 ? 8 : 4);
   const int64_t fit = 3 * p.W;
+  const int64_t slots = cus * (16 / p.W), fits = kParkBytes / (16 * 64 * p.BV);   // 64 W BV bytes a tile, 16 / W workgroups
   p.KG = std::min((KC + fit - 1) / fit, most);
-  // few tiles: more K groups use the idle compute units and leave each less of
-  // x to convert, which pays for the reduction pass where there is one anyway
-  // or the batch is large (batch 16: 512 x 12288 11.9 -> 8.2 us, 2048 x 6144
-  // 10.1 -> 9.5)
-  if (T * p.KG <= cus && (p.KG > 1 || (B > 8 && KC > 40)))
+  // chunks of the busiest wavefront over its workgroup's tiles
+  auto load = [&](int64_t KG) {
+    const int64_t groups = std::min<int64_t>(T, std::max<int64_t>(1, slots / KG));
+    return (T + groups - 1) / groups * (((KC + KG - 1) / KG + p.W - 1) / p.W);
+  };
+  if (bits != 4 && p.KG > 1 && deep && T <= cus * fits && (B <= 4 || (B <= 8 && KC <= 64))) {
+    // LUT, many tiles: passes need no reduction launch, and every compute unit
+    // still converts each part of x once (groups against passes: 65536 x 6176
+    // at batch 4 39.4 / 38.1 us, 12288 x 8192 15.2 / 13.1, 49168 x 12288 at
+    // batch 2 52.1 / 47.3; at batch 8 12288 x 8192 15.2 / 13.9, but 12288 x
+    // 17408 25.9 / 26.7; 5120 x 12288 at batch 2 11.8 / 12.3).  Rows just above
+    // 48 chunks pay most for the second pass: 65536 x 6176 at batch 4 40.6
+    // against 38.9 in the kernel with K groups staged in LDS, whose like this
+    // kernel otherwise is or beats (7168 columns: 39.6 against 42.9)
+    p.KG = 1;
+  } else if (T * p.KG <= cus && (p.KG > 1 || (B > 8 && (KC > 40 || (KC > 32 && 3 * T <= cus))))) {
+    // few tiles: more K groups use the idle compute units and leave each less
+    // of x to convert, which pays for the reduction pass where there is one
+    // anyway or the batch is large (batch 16: 512 x 12288 11.9 -> 8.2 us,
+    // 2048 x 6144 10.1 -> 9.5; 1040 x 5120 8.8 -> 7.8, but 2048 x 4608 at
+    // batch 12 7.8 / 8.3)
     p.KG = std::min(most, std::max(p.KG, std::min((KC + p.W - 1) / p.W, (B > 8 ? 2 : 1) * cus / T)));
+  } else if (p.KG > 1 && p.KG < most && T * p.KG <= 4 * cus && load(p.KG + 1) <= load(p.KG)) {
+    // one group more where that leaves no wavefront more to do (batch 16:
+    // 2048 x 17408 14.0 -> 12.7 us, 4096 x 17408 16.9 -> 15.2, 5120 x 12288
+    // 15.3 -> 14.0; with more tiles the partial sums cost more than it gives:
+    // 49168 x 12288 at batch 12 53.0 / 54.0)
+    ++p.KG;
+  }
   p.KCR = (KC + p.KG - 1) / p.KG;
   p.KG = (KC + p.KCR - 1) / p.KCR;
   const int64_t passes = (p.KCR + fit - 1) / fit;
   p.CPW = (p.KCR + passes * p.W - 1) / (passes * p.W);
-  const int64_t slots = cus * (16 / p.W), fits = kParkBytes / (16 * 1024);   // W KiB a tile, 16 / W workgroups
   int64_t groups = std::min<int64_t>(T, std::max<int64_t>(1, slots / p.KG));
   if (passes > 1)   // every tile stays parked over the passes: whole rounds of fuller workgroups
     groups *= (T + groups * fits - 1) / (groups * fits);

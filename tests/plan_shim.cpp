@@ -10,11 +10,11 @@ int64_t gemv_contract_groups(int64_t B, int64_t T, int64_t KC, int64_t cus) {
   return dq::contract_groups(B, T, KC, cus);
 }
 
-// out: ok, W, CPW, KG, KCR, TPG, G, park
+// out: ok, BV, W, CPW, KG, KCR, TPG, G, park
 void gemv_plan(int bits, int64_t B, int64_t T, int64_t KC, int64_t most, int64_t cus, int64_t* out) {
   const dq::BatchedPlan p = dq::plan_batched(bits, B, T, KC, most, cus);
-  const int64_t v[8] = {p.ok, p.W, p.CPW, p.KG, p.KCR, p.TPG, p.G, p.park};
-  for (int i = 0; i < 8; ++i) out[i] = v[i];
+  const int64_t v[9] = {p.ok, p.BV, p.W, p.CPW, p.KG, p.KCR, p.TPG, p.G, p.park};
+  for (int i = 0; i < 9; ++i) out[i] = v[i];
 }
 
 // Walks the code (scales = 0) or block-scale loads of the first and the last

@@ -10,7 +10,7 @@ import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2609_26333_amd", "csrc")
-GemvPlan = collections.namedtuple("GemvPlan", "ok W CPW KG KCR TPG G park")
+GemvPlan = collections.namedtuple("GemvPlan", "ok BV W CPW KG KCR TPG G park")
 
 
 @functools.lru_cache(None)
@@ -33,7 +33,7 @@ def gemv_plan(bits, B, N, K, most=None, cus=256):
     T, KC = (N + 15) // 16, (K + 127) // 128
     if most is None:
         most = shim().gemv_contract_groups(B, T, KC, cus)
-    out = (ctypes.c_int64 * 8)()
+    out = (ctypes.c_int64 * 9)()
     shim().gemv_plan(bits, B, T, KC, most, cus, out)
     return GemvPlan(*out)
 

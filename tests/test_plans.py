@@ -39,3 +39,18 @@ def test_gemv_plan_loads(bits):
                 assert p.park == p.TPG
             for scales in (0, 1):
                 assert plans.gemv_bad_loads(bits, B, N, K, m, scales) == 0, (bits, N, K, B, m, scales)
+
+
+@pytest.mark.parametrize("bits", [2, 3])
+def test_gemv_plan_converts_once(bits):
+    """LUT, many tiles, more than 48 chunks: no compute unit gets a second
+    workgroup (which would convert x again), small batches need no reduction
+    launch, and no launch leaves a quarter of the compute units idle."""
+    for N in (16384, 49168, 65536, 100000, 147456):
+        for K in (6176, 8192, 12288, 17408):
+            for B in (2, 3, 4):
+                p = plans.gemv_plan(bits, B, N, K)
+                assert p.G <= 256 and p.KG == 1, (N, K, B, p)
+    for N in (2048, 4096, 5120):
+        for K in (12288, 17408):
+            assert plans.gemv_plan(bits, 16, N, K).G > 192, (N, K)
