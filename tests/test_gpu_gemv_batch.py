@@ -1,8 +1,8 @@
 """LUT GEMV at batch >= 2 (activations in registers), at the edges of its
 plan: rows of 1 to 136 chunks (4, 8 and 16 wavefronts, 1 to 3 chunks each,
-K groups, wavefronts with one chunk less), one to many row tiles per
-workgroup, the three batch widths, both table modes, against the fp64 oracle
-element by element."""
+K groups, passes, wavefronts with one chunk less), one to many row tiles per
+workgroup (more than are parked in LDS at once among them), the three batch
+widths, both table modes, against the fp64 oracle element by element."""
 import os
 import sys
 
@@ -12,6 +12,7 @@ import torch
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import parity_bounds as PB  # noqa: E402
+import plans  # noqa: E402
 
 import synth  # noqa: E402
 from oracle import formats, linalg, lut  # noqa: E402
@@ -49,8 +50,12 @@ def check(w, Wq, xb, rows, bits, mode, what):
         bound = PB.gemv_bound(formats.f64_from_bf16_bits(xb), what_hat, K)
     else:
         grid = lut.default_grid(bits)
-        codes, sb, G = lut.quantize_paper_grid(w, grid)
-        codes, sb = codes[rows], sb[rows]
+        if isinstance(w, _Rows):   # the rows' codes under the whole weight's scale
+            codes, sb, G = lut.quantize_paper_grid(np.vstack([w[rows], w.largest()]), grid)
+            codes, sb = codes[:-1], sb[:-1]
+        else:
+            codes, sb, G = lut.quantize_paper_grid(w, grid)
+            codes, sb = codes[rows], sb[rows]
         ref, what_hat = linalg.lut_gemv_paper(xb, codes, sb, G, grid), lut.dequantize_paper_grid(codes, sb, G, grid)
         bound = PB.gemv_bound(formats.f64_from_bf16_bits(xb), what_hat, K, folded_rel=2.0 ** -11)
     PB.assert_within(y.cpu().numpy()[:, rows], ref, bound, what)
@@ -72,17 +77,32 @@ def test_gemv_batch(N, K, B, bits, mode):
     check(w, Wq, xb, rows, bits, mode, "gemv batch")
 
 
-def test_gemv_batch_passes():
-    """Batch 2 of a weight so tall that the workspace holds one K group and too
-    wide for one: the activations are taken in two passes over the tiles."""
-    N, K, B = 49200, 6272, 2
+# More tiles per workgroup than are parked at once (9, 18 and 36 at the three
+# batch widths), with one K group and with several, and passes over the parked
+# tiles (every one of them parked); a ragged last workgroup each.
+MANY = [(39900, 3200, 16, "one group"), (79900, 3232, 8, "one group"), (149900, 3200, 3, "one group"),
+        (19900, 12000, 16, "groups"), (39900, 12000, 8, "groups"), (149900, 6400, 4, "groups"),
+        (49200, 6272, 2, "passes"), (65400, 8224, 4, "passes"), (16200, 6176, 7, "passes"), (100100, 12320, 3, "passes")]
+
+
+@pytest.mark.parametrize("N,K,B,kind", MANY)
+@pytest.mark.parametrize("bits,mode", [(3, 0), (2, 1)])
+def test_gemv_batch_many_tiles(N, K, B, kind, bits, mode):
+    print("gemv many tiles", N, K, B, kind, bits, mode, flush=True)
+    p = plans.gemv_plan(bits, B, N, K, cus=torch.cuda.get_device_properties(0).multi_processor_count)
+    assert (p.KG > 1) == (kind == "groups") and (p.KCR > p.W * p.CPW) == (kind == "passes"), p
+    assert p.park == p.TPG if kind == "passes" else p.park < p.TPG, p
     g = torch.Generator(device="cuda").manual_seed(3)
     w = torch.randn((N, K), generator=g, device="cuda").mul_(0.02)
-    Wq = dq.dq_pack_lut3(w, bits=3)
-    assert dq.dq_decode_gemv_workspace_size(B, Wq) == 0
+    Wq = dq.dq_pack_lut3(w, bits=bits, mode=mode)
     xb = synth.random_bf16(12, (B, K), outlier_frac=0.005, outlier_factor=30)
-    rows = np.unique(np.r_[0:16, N - 20:N, np.random.default_rng(5).choice(N, 100)])
-    check(_Rows(w), Wq, xb, rows, 3, dq.LUT_PER_ROW, "gemv passes")
+    T, rng = (N + 15) // 16, np.random.default_rng(5)
+    tiles = [0, T - 1, T - 2]   # around the parks and the ends of some workgroups
+    for wg in (0, 1, p.G // p.KG - 2, p.G // p.KG - 1):
+        tiles += [wg * p.TPG + t for t in (0, p.park - 1, p.park, 2 * p.park, p.TPG - 1) if t < p.TPG]
+    tiles = np.unique(np.clip(tiles, 0, T - 1))
+    rows = np.unique(np.r_[(tiles[:, None] * 16 + [0, 7, 15]).ravel(), N - 1, rng.choice(N, 40)])
+    check(_Rows(w), Wq, xb, rows[rows < N], bits, mode, "gemv many tiles")
 
 
 class _Rows:
@@ -93,6 +113,10 @@ class _Rows:
 
     def __getitem__(self, rows):
         return self.t[torch.from_numpy(np.asarray(rows)).cuda()].cpu().numpy()
+
+    def largest(self):
+        """The row that holds the largest magnitude."""
+        return self.t[self.t.abs().amax(1).argmax()].cpu().numpy()[None]
 
 
 def test_gemv_batch_scales_per_row():

@@ -12,6 +12,7 @@ import torch
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import parity_bounds as PB  # noqa: E402
+import plans  # noqa: E402
 
 import synth  # noqa: E402
 from oracle import formats, linalg, nvfp4  # noqa: E402
@@ -35,8 +36,10 @@ def dev(a):
 
 
 def check(w, xb, rows):
+    """w: on the host, or on the GPU (then only its rows are compared)."""
     (B, K), N = xb.shape, w.shape[0]
-    Wq = dq.dq_pack_nvfp4(dev(w))
+    on_gpu = isinstance(w, torch.Tensor)
+    Wq = dq.dq_pack_nvfp4(w if on_gpu else dev(w))
     x = dev(xb.view(np.int16))
     y = dq.dq_decode_gemv_nvfp4(x, Wq, out_kind=dq.OUT_F32)
     yb = dq.dq_decode_gemv_nvfp4(x, Wq, out_kind=dq.OUT_BF16)
@@ -46,8 +49,12 @@ def check(w, xb, rows):
                                          torch.cuda.current_stream().cuda_stream) == dq.DQ_OK
     torch.cuda.synchronize()
     assert torch.equal(y, yp) and torch.equal(yb, y.bfloat16())
-    q, c, G = nvfp4.quantize_dynamic(w)
-    q, c = q[rows], c[rows]
+    if on_gpu:   # the rows' codes under the whole weight's scale
+        G = nvfp4.global_scale(np.float32(w.abs().max().item()))
+        q, c = nvfp4.quantize(w[torch.from_numpy(rows).cuda()].cpu().numpy(), G)
+    else:
+        q, c, G = nvfp4.quantize_dynamic(w)
+        q, c = q[rows], c[rows]
     bound = PB.gemv_bound(formats.f64_from_bf16_bits(xb), nvfp4.dequantize(q, c, G), K)
     PB.assert_within(y.cpu().numpy()[:, rows], linalg.nvfp4a16_gemv(xb, q, c, G), bound, "nvfp4 gemv")
 
@@ -65,6 +72,31 @@ def test_gemv_nvfp4(N, K, B):
     xb = synth.random_bf16(B + K, (B, K), outlier_frac=0.005, outlier_factor=30)
     rows = np.arange(N) if N * K <= 1 << 20 else np.unique(np.r_[0:33, N - 20:N, np.random.default_rng(N).choice(N, 60)])
     check(w, xb, rows)
+
+
+# More tiles per workgroup than are parked at once (9, 18 and 36 at the three
+# batch widths), with one K group and with several; a ragged last workgroup each
+MANY = [(39900, 3216, 16, 1), (79900, 3200, 7, 1), (149900, 3200, 1, 1), (19900, 12016, 16, 2), (39900, 8208, 6, 2),
+        (149900, 6416, 2, 2)]
+
+
+@pytest.mark.parametrize("N,K,B,groups", MANY)
+def test_gemv_nvfp4_many_tiles(N, K, B, groups):
+    print("nvfp4 gemv many tiles", N, K, B, flush=True)
+    T = (N + 15) // 16
+    need = dq.dq_decode_gemv_nvfp4_workspace_size(B, dq.NvFp4Tensor.empty(N, K))
+    p = plans.gemv_plan(4, B, N, K, most=max(1, need // (T * B * 64)),
+                        cus=torch.cuda.get_device_properties(0).multi_processor_count)
+    assert p.KG == groups and p.park < p.TPG and p.KCR <= p.W * p.CPW, p
+    g = torch.Generator(device="cuda").manual_seed(3)
+    w = torch.randn((N, K), generator=g, device="cuda").mul_(0.02)
+    xb = synth.random_bf16(12, (B, K), outlier_frac=0.005, outlier_factor=30)
+    tiles = [0, T - 1, T - 2]
+    for wg in (0, 1, p.G // p.KG - 2, p.G // p.KG - 1):
+        tiles += [wg * p.TPG + t for t in (0, p.park - 1, p.park, 2 * p.park, p.TPG - 1) if t < p.TPG]
+    tiles = np.unique(np.clip(tiles, 0, T - 1))
+    rows = np.unique(np.r_[(tiles[:, None] * 16 + [0, 7, 15]).ravel(), N - 1, np.random.default_rng(5).choice(N, 40)])
+    check(w, xb, rows[rows < N])
 
 
 def test_gemv_nvfp4_scales_per_row():
