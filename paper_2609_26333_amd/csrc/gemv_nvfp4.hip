@@ -121,12 +121,12 @@ __global__ __launch_bounds__(256) void nvfp4_gemv_kernel(const uint16_t* __restr
     const bool ok = t < T;
     const v4i_t rc = nv_resource(codes + ((int64_t)(ok ? t : 0) * KT + kt0) * 1024, ok ? (uint32_t)valid * 1024u : 0u);
     const v4i_t rs = nv_resource(scales + ((int64_t)(ok ? t : 0) * KT + kt0) * 128, ok ? (uint32_t)valid * 128u : 0u);
+    const int st = min(st0, ok ? valid : 0);   // (the uniform offset stays within the resource)
 #pragma unroll
     for (int u = 0; u < kCyc; ++u) {
-      const int st = min(st0 + u, ok ? valid : 0);   // (the uniform offset stays within the resource)
-      const v4i_t v = nv_buffer_load_b128(rc, c_off, st * 1024, 0);
+      const v4i_t v = nv_buffer_load_b128(rc, c_off + u * 1024, st * 1024, 0);
       cb.c[u] = uint4_t{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
-      cb.s[u] = (uint16_t)nv_buffer_load_b16(rs, s_off, st * 128, 0);
+      cb.s[u] = (uint16_t)nv_buffer_load_b16(rs, s_off + u * 128, st * 128, 0);
     }
   };
   issue(0, cb0);
@@ -243,9 +243,9 @@ __global__ __launch_bounds__(256) void nvfp4_gemv_kernel(const uint16_t* __restr
   if (q < cycles) consume(q, cb0);
 }
 
-// One-launch kernel for batch 1 and 2 (the staged slices within 48 KiB of LDS)
-// and at most one resident round of row tiles (16 wavefronts per compute
-// unit).  A workgroup of kKsWaves (4 or 8) wavefronts takes one
+// One-launch kernel for small batches (the staged slices within 48 KiB of LDS;
+// see ks_better) and at most one resident round of row tiles (16 wavefronts
+// per compute unit).  A workgroup of kKsWaves (4 or 8) wavefronts takes one
 // row tile;
 // wavefront w takes K steps [w SPW, (w + 1) SPW).  It copies its own slice of
 // x straight into LDS (issued before its code loads, so the copy is not
@@ -298,12 +298,12 @@ __global__ __launch_bounds__(64 * kKsWaves) void nvfp4_gemv_ks_kernel(
   };
   Cycle cb0, cb1;
   auto issue = [&](int q, Cycle& cb) {
+    const int st = min(kCyc * q, nst);   // (the uniform offset stays within the resource)
 #pragma unroll
     for (int u = 0; u < kCyc; ++u) {
-      const int st = min(kCyc * q + u, nst);   // (the uniform offset stays within the resource)
-      const v4i_t v = nv_buffer_load_b128(rc, c_off, st * 1024, 0);
+      const v4i_t v = nv_buffer_load_b128(rc, c_off + u * 1024, st * 1024, 0);
       cb.c[u] = uint4_t{(uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]};
-      cb.s[u] = (uint16_t)nv_buffer_load_b16(rs, s_off, st * 128, 0);
+      cb.s[u] = (uint16_t)nv_buffer_load_b16(rs, s_off + u * 128, st * 128, 0);
     }
   };
   __builtin_amdgcn_sched_barrier(0);
@@ -470,18 +470,35 @@ KsPlan ks_plan(int64_t B, int64_t N, int64_t K) {
   return p;
 }
 
-// Where the one-launch kernel is still faster than the batched one (measured
-// over N = 512 .. 65536, K = 512 .. 17408, batch 1 .. 16):
-// - batch 1 or 2 with one to two 16-row tiles per compute unit and more than
-//   1024 columns: the batched kernel leaves compute units without a second
-//   tile and converts all of x on each (6144 x 6144 at batch 1 8.0 us against
-//   9.8, batch 2 8.8 against 9.9; batch 3 9.7 against 10.0, batch 4 14.6
-//   against 10.2);
-// - batch 1 with more than 6144 columns, where it takes x in passes (no
-//   workspace at batch 1; 2048 x 17408 13.6 against 14.3).
+// Where the one-launch kernel is the faster one (batched / this, measured over
+// N = 1024 .. 30720, K = 512 .. 17408, batch 1 .. 4; P = 16-row tiles per
+// compute unit, rounded up).  Its tiles of 32 rows fit an even P, where the
+// batched kernel converts all of x on every compute unit for few tiles:
+// - batch 1, P = 2 or 4: 1.03-1.4 above 512 columns (0.95 at 512; 6144 x 6144
+//   11.0 against 8.1 us, 14336 x 3072 11.2 / 8.6);
+// - batch 2: 1.15 at 2049..3072 columns (which half fill the batched kernel's
+//   second chunk), 1.06-1.5 above 4096, 0.97-1.05 between; 513..2048 columns
+//   0.97-1.04 at P = 2, 0.95-1.01 at P = 4;
+// - batch 3: 1.04-1.09 at 2049..3072, 0.90-0.97 between, above 4096 1.07-1.2 at
+//   P = 2 and at P = 4 0.97-1.02, 1.06 above 6144;
+// - batch 4: P = 2 above 4096 columns 1.01-1.05, else 0.65-1.0;
+// - any other P, batch 1: 1.02-1.11 at 2049..3072 columns and 1.00-1.04 at
+//   513..1024; above 6144, where the batched kernel takes x in passes (no
+//   workspace at batch 1), 1.05-1.17 at P = 1 and, at P = 3, 0.91-0.97 up to
+//   8192 and 0.95-1.11 beyond; P = 1 with at least half the compute units busy
+//   above 4096 columns 1.00-1.04; batch 2 above 8192 columns 1.01-1.07; P = 8
+//   (the last that fits) 1.02-1.11 above 2048 columns, 1.03 at batch 2.
 bool ks_better(int64_t B, int64_t N, int64_t K) {
-  const int64_t T = (N + 15) / 16, cus = num_cus();
-  return ks_plan(B, N, K).ok && ((B <= 2 && T > cus && T <= 2 * cus && K > 1024) || (B == 1 && K > 6144));
+  const int64_t T = (N + 15) / 16, cus = num_cus(), P = (T + cus - 1) / cus;
+  const bool even = P == 2 || P == 4, half = K > 2048 && K <= 3072;
+  bool better = false;
+  if (B == 1)
+    better = (even && K > 512) || (P == 8 && K > 2048) || (P > 1 && (half || (K > 512 && K <= 1024))) ||
+             K > (P == 3 ? 8192 : 6144) || (P == 1 && 2 * T >= cus && K > 4096);
+  if (B == 2) better = (P == 2 && K > 512) || (P == 4 && K > 2048) || (P == 8 && half) || K > 8192;
+  if (B == 3) better = (even && half) || (P == 2 && K > 4096) || (P == 4 && K > 6144);
+  if (B == 4) better = P == 2 && K > 4096;
+  return better && ks_plan(B, N, K).ok;
 }
 
 }  // namespace

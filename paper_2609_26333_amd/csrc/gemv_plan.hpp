@@ -89,6 +89,20 @@ inline BatchedPlan plan_batched(int bits, int64_t B, int64_t T, int64_t KC, int6
   p.BV = B > 8 ? 16 : B > 4 ? 8 : 4;
   const bool deep = T >= 2 * cus;
   p.W = deep ? (KC > 24 ? 16 : KC > 12 ? 8 : 4) : (KC > 8 ? 16 : KC > 4 ? 8 : 4);
+  // but sixteen where two workgroups of eight would take two tiles each and one
+  // of sixteen takes three (LUT3 10240 x 3072 at batch 2 7.8 -> 7.1 us, NVFP4
+  // 10.9 -> 8.8)
+  if (p.W == 8 && deep && T > 2 * cus && T <= 3 * cus) p.W = 16;
+  // NVFP4 streams more bytes per chunk and gains less from the shared set-up
+  // than it loses on converting x in every workgroup (batch 1, four or eight
+  // against sixteen wavefronts: 18432 x 1280 8.8 / 7.7 us, 12288 x 2048 8.3 /
+  // 6.6, but 24576 x 2560 11.9 / 14.1, 8192 x 1280 5.3 / 5.6, 65536 x 1056
+  // 14.9 / 15.5; four against eight: 16384 x 768 6.1 / 5.5, 12288 x 768 5.0 /
+  // 5.4)
+  if (bits == 4 && deep) {
+    if (KC > (T > 2 * cus ? 8 : 12) && (T <= (KC <= 16 ? 8 : 5) * cus || B > 8)) p.W = 16;
+    else if (KC > 4 && KC <= 8 && T > 3 * cus) p.W = 8;
+  }
   const int64_t fit = 3 * p.W;
   const int64_t slots = cus * (16 / p.W), fits = kParkBytes / (16 * 64 * p.BV);   // 64 W BV bytes a tile, 16 / W workgroups
   p.KG = std::min((KC + fit - 1) / fit, most);

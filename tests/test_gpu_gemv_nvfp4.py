@@ -62,7 +62,12 @@ def check(w, xb, rows):
 CASES = [(5, 16, 2), (16, 48, 16), (33, 64, 5), (100, 80, 3), (47, 144, 9), (520, 512, 16), (40, 1040, 4),
          (4096, 1040, 1), (4112, 1024, 2), (4112, 1040, 2), (4112, 1040, 3), (8192, 1088, 2), (8208, 1104, 2),
          (8200, 1552, 8), (8200, 3088, 7), (8200, 3104, 12), (9000, 4096, 11), (250, 6144, 16), (300, 6160, 3),
-         (300, 6160, 1), (2050, 7184, 12), (70, 8208, 2), (40, 12304, 16), (2050, 17408, 6), (70, 17408, 8)]
+         (300, 6160, 1), (2050, 7184, 12), (70, 8208, 2), (40, 12304, 16), (2050, 17408, 6), (70, 17408, 8),
+         # both sides of the rule at two, three, four and eight tiles per compute unit, and of the plan's
+         # wavefronts per workgroup (4, 8 and 16 for short rows)
+         (4112, 528, 1), (8192, 512, 1), (8208, 2064, 1), (8208, 2048, 1), (12304, 784, 2), (12304, 2576, 2),
+         (16384, 4112, 3), (5120, 4112, 4), (5120, 4096, 4), (12288, 1040, 2), (16400, 1552, 3), (16400, 784, 8),
+         (20496, 2576, 4), (30720, 2064, 2), (32784, 1040, 2), (3072, 4112, 1)]
 
 
 @pytest.mark.parametrize("N,K,B", CASES)
