@@ -780,7 +780,7 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
         const i32x2_t v = raw_buffer_load_b64(rcodes, a.lane, a.uniform, 0);
         ring[r][u].w[2 * h] = (uint32_t)v[0];
         ring[r][u].w[2 * h + 1] = (uint32_t)v[1];
-        sring[r][u][h] = (uint32_t)raw_buffer_load_b32(rscales, a.lane_scale, a.uniform / 8, 0);
+        sring[r][u][h] = (uint32_t)raw_buffer_load_b32(rscales, a.lane_scale, (int32_t)((uint32_t)a.uniform >> 3), 0);
       }
     } else {
       const LoadAt a = lut_chunk_at(ok, t0 + t, KC, c, lane_code, lane_scale & ~3);
@@ -941,7 +941,10 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
       for (int p = wave; p < parked; p += W) {
         const float4_t* pr = part + p * W * kSlot + lane_slot;
         float4_t o = pr[0];
-#pragma unroll 4
+        // (four ahead spilled an activation fragment of this instance, and its
+        // reload waited for every code load once a tile)
+        constexpr int kReads = MODE == 2 && CPW == 3 && BV == 16 ? 2 : 4;
+#pragma unroll kReads
         for (int w2 = 1; w2 < W; ++w2) {
           const float4_t t2 = pr[w2 * kSlot];
 #pragma unroll

@@ -41,14 +41,14 @@ DQ_HOST_DEVICE inline LoadAt lut_chunk_at(bool wanted, int tile, int KC, int chu
 // NVFP4: a chunk's first K step in half of the 32-row tile `pair`, in bytes of
 // codes from the start of the buffer
 DQ_HOST_DEVICE inline int32_t nvfp4_chunk_at(bool wanted, int pair, int KT, int chunk, int half) {
-  return wanted ? (pair * KT + 2 * chunk) * 1024 + half * 512 : 0;
+  return ((pair * KT + 2 * chunk) * 1024 + half * 512) & -(int32_t)wanted;   // (no branch around the loads)
 }
 // and its K step `step` (h = 0 or 1), which the last chunk of an odd KT lacks
 // (the scales at `uniform` / 8)
 DQ_HOST_DEVICE inline LoadAt nvfp4_step_at(bool wanted, int32_t chunk_at, int step, int KT, int h, int32_t lane,
                                            int32_t lane_scale) {
   const bool in = h == 0 ? wanted : wanted && step < KT;
-  return LoadAt{in ? lane : kNowhere, h == 0 ? chunk_at : in ? chunk_at + 1024 : 0, in ? lane_scale : kNowhere};
+  return LoadAt{in ? lane : kNowhere, h == 0 ? chunk_at : (chunk_at + 1024) & -(int32_t)in, in ? lane_scale : kNowhere};
 }
 
 // K groups whose partial sums the workspace of a batch B >= 2 call holds (the
