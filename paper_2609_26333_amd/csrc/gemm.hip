@@ -43,6 +43,7 @@
 
 #include "dq_device.hpp"
 #include "dq_internal.hpp"
+#include "gemm_plan.hpp"
 
 namespace dq {
 
@@ -768,7 +769,6 @@ GemmOut gemm_out(const GemmArgs& a) {
 int64_t short_columns(const GemmArgs& a) {
   return a.out_kind != kOutNvfp4 ? a.N : round_up(a.N, (a.flags & 1) != 0 ? 128 : 64);
 }
-int64_t short_tiles(int64_t n, int t) { return (n + 32 * t - 1) / (32 * t); }
 
 template <class Gm>
 hipError_t launch_short(const GemmArgs& a, hipStream_t s) {
@@ -831,65 +831,10 @@ hipError_t launch_geo(const GemmArgs& a, int64_t split, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Modelled time (us) of a grid, for the choice between the kernels.  Both
-// sides were measured on 230 combinations of M = 16 .. 4096 with the 8B and
-// 27B linears and 1024 x 4096, 1024 x 16384, 3072 x 768; the model is within
-// 7-10 % of either, and the choice within 1 % of the faster kernel on average
-// (on 460 random shapes up to 8192 rows, within 1.8 % of the fastest of all).
-// Ring kernels: per K step, by resident workgroups (1 or 2 per compute unit)
-// and then by the total of 256 x 128 tiles.
-double ring_time(int64_t M, int64_t N, int64_t KT, int64_t cus) {
-  const int64_t t = ((M + 255) / 256) * ((N + 127) / 128);
-  if (t <= cus) {
-    const int64_t half = ((M + 127) / 128) * ((N + 127) / 128);   // 128 x 128 tiles
-    return 3.0 + (half <= cus ? 0.50 : 0.90) * (double)KT;
-  }
-  const double x = (double)t * 256.0 / (double)cus;
-  return 3.0 + (t <= 2 * cus ? 1.1 + 0.0008 * x : 0.55 + 0.0026 * x) * (double)KT;
-}
-
-// Short-grid tiles: `conc` workgroups per compute unit (by registers); `fixed`
-// per round of them (ring fill, reduction, store), `step` per K step and
-// workgroup on the fullest compute unit, growing by `crowd` with their number.
-struct ShortFit {
-  int tm, tn, conc;
-  double fixed, step, crowd;
-  hipError_t (*launch)(const GemmArgs&, hipStream_t);
-};
-
-double short_time(const ShortFit& f, int64_t M, int64_t cols, int64_t KT, int64_t cus) {
-  const int64_t tiles = short_tiles(M, f.tm) * short_tiles(cols, f.tn);
-  const double rounds = (double)((tiles + cus * f.conc - 1) / (cus * f.conc)), load = (double)((tiles + cus - 1) / cus);
-  return 3.0 + f.fixed * rounds + f.step * (double)KT * load * (1.0 + f.crowd * (1.0 - 1.0 / load));
-}
-
-// The short-grid tile to use, or NULL for the ring kernels: the faster of the
-// two by the models, 5 % to the ring kernels.  Measured, bf16 out, M = 168:
-// 27B o 42.1 -> 13.3 us, q/k/v 42.6 -> 17.4, down 130 -> 37.3, gate/up 109 ->
-// 67; 8B up 38 -> 23; at M = 1024 down 222 -> 162, o 70 -> 55 and gate/up 294
-// against 313 with the short grid (not used).
-const ShortFit* choose_short(const GemmArgs& a, int64_t cus) {
-  static const ShortFit fits[] = {{1, 1, 2, 1.65, 0.0439, 0.0, launch_short<ShortGeo<1, 1, 8, 4>>},
-                                  {1, 2, 2, 2.26, 0.0626, 0.06, launch_short<ShortGeo<1, 2, 8, 4>>},
-                                  {2, 2, 1, 2.55, 0.0895, 0.33, launch_short<ShortGeo<2, 2, 8, 3>>},
-                                  {3, 2, 2, 3.19, 0.1286, 0.14, launch_short<ShortGeo<3, 2, 4, 2>>},
-                                  {2, 3, 2, 3.68, 0.1279, 0.16, launch_short<ShortGeo<2, 3, 4, 2>>},
-                                  {4, 2, 1, 4.53, 0.1454, 0.40, launch_short<ShortGeo<4, 2, 8, 2>>}};
-  // (columns in whole 128s: the same tile, and so the same sums, whatever the
-  // output kind)
-  const int64_t KT = round_up(a.K, 64) / 64, cols = round_up(a.N, 128);
-  if (KT == 0) return nullptr;
-  double best = 0.95 * ring_time(a.M, a.N, KT, cus);
-  const ShortFit* pick = nullptr;
-  for (const ShortFit& f : fits) {
-    const double t = short_time(f, a.M, cols, KT, cus);
-    if (t < best) {
-      best = t;
-      pick = &f;
-    }
-  }
-  return pick;
-}
+// The short-grid kernel's launchers, in the order of kShortFits
+hipError_t (*const kShortLaunch[kNumShortFits])(const GemmArgs&, hipStream_t) = {
+    launch_short<ShortGeo<1, 1, 8, 4>>, launch_short<ShortGeo<1, 2, 8, 4>>, launch_short<ShortGeo<2, 2, 8, 3>>,
+    launch_short<ShortGeo<3, 2, 4, 2>>, launch_short<ShortGeo<2, 3, 4, 2>>, launch_short<ShortGeo<4, 2, 8, 2>>};
 
 }  // namespace
 
@@ -903,7 +848,8 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     return hipGetLastError();
   }
   const int cus = num_cus();
-  if (const ShortFit* f = choose_short(a, cus)) return f->launch(a, s);
+  const int fit = choose_short(a.M, a.N, a.K, cus);
+  if (fit >= 0) return kShortLaunch[fit](a, s);
   // bf16 output without SwiGLU on grids of at least two full rounds of
   // 256x256 tiles: one workgroup of four 128x128 wavefronts per compute unit
   // (one wavefront per SIMD, 256 accumulator registers).  A wavefront

@@ -2,6 +2,7 @@
 // tests/plans.py.
 #include <cstdint>
 
+#include "gemm_plan.hpp"
 #include "gemv_plan.hpp"
 
 extern "C" {
@@ -66,6 +67,12 @@ int64_t gemv_bad_loads(int bits, int64_t B, int64_t T, int64_t KC, int64_t KT, i
       }
   }
   return bad;
+}
+
+// rows * 100 + columns of the short-grid tile in 32s, or -1 for the ring kernels
+int gemm_short_tile(int64_t M, int64_t N, int64_t K, int64_t cus) {
+  const int f = dq::choose_short(M, N, K, cus);
+  return f < 0 ? -1 : dq::kShortFits[f].tm * 100 + dq::kShortFits[f].tn;
 }
 
 }  // extern "C"

@@ -24,6 +24,7 @@ def shim():
     lib.gemv_contract_groups.argtypes, lib.gemv_contract_groups.restype = [i64] * 4, i64
     lib.gemv_plan.argtypes, lib.gemv_plan.restype = [i32] + [i64] * 5 + [ctypes.POINTER(i64)], None
     lib.gemv_bad_loads.argtypes, lib.gemv_bad_loads.restype = [i32] + [i64] * 6 + [i32], i64
+    lib.gemm_short_tile.argtypes, lib.gemm_short_tile.restype = [i64] * 4, i32
     return lib
 
 
@@ -40,3 +41,9 @@ def gemv_plan(bits, B, N, K, most=None, cus=256):
 
 def gemv_bad_loads(bits, B, N, K, most, scales, cus=256):
     return shim().gemv_bad_loads(bits, B, (N + 15) // 16, (K + 127) // 128, (K + 63) // 64, most, cus, scales)
+
+
+def gemm_short_tile(M, N, K, cus=256):
+    """(rows, columns) in 32s of the NVFP4 GEMM's short-grid tile; None: the ring kernels."""
+    v = shim().gemm_short_tile(M, N, K, cus)
+    return None if v < 0 else divmod(v, 100)

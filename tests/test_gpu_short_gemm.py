@@ -1,6 +1,7 @@
 """NVFP4 GEMM on short grids: the kernel that splits K over the wavefronts of
 a workgroup, at the edges of its tiles (rows, columns and K steps that end
-inside one, wavefronts without a K step) and for every tile shape, against the
+inside one, wavefronts without a K step, ring cycles that end early) and for
+every tile shape, and shapes on the ring kernels' side of the rule, against the
 fp64 oracle of the GPU's own operand codes and the oracle quantizer."""
 import os
 import sys
@@ -12,6 +13,7 @@ import torch
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import dq_layout as L  # noqa: E402
 import parity_bounds as PB  # noqa: E402
+import plans  # noqa: E402
 
 import synth  # noqa: E402
 from oracle import linalg, nvfp4  # noqa: E402
@@ -34,15 +36,33 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-# rows from 1 to several tiles, columns that are no multiple of a tile, of 16
-# or of 4, K from a quarter step to more steps than wavefronts; the last ones
-# take the larger tiles (96 x 64, 64 x 96, 128 x 64) on a 256-CU device
-SHAPES = [(1, 16, 16), (16, 48, 64), (33, 100, 80), (64, 97, 512), (65, 224, 528), (96, 1000, 1040), (130, 352, 2048),
-          (168, 4096, 576), (168, 34816, 64), (250, 6144, 512), (384, 5120, 640), (160, 8192, 320), (700, 3000, 272)]
+# (M, N, K), and the tile in 32s that a 256-CU device takes for it (None: the
+# ring kernels).  Columns that are no multiple of a tile, of 16 or of 4; K from
+# a quarter step to 26 steps, so that wavefronts have three steps, one or none.
+SHAPES = [((1, 16, 16), None), ((16, 48, 64), None), ((33, 100, 80), None), ((168, 34816, 64), None),
+          ((250, 6144, 512), None), ((384, 5120, 640), None), ((160, 8192, 320), None), ((700, 3000, 272), None),
+          ((64, 97, 512), (1, 1)), ((65, 224, 528), (1, 1)), ((96, 1000, 1040), (1, 1)), ((130, 352, 2048), (1, 1)),
+          ((33, 1000, 272), (1, 1)),
+          ((70, 8224, 592), (1, 2)), ((161, 1504, 1616), (1, 2)), ((33, 6200, 1616), (1, 2)),
+          ((168, 4096, 576), (2, 2)), ((161, 3040, 528), (2, 2)), ((70, 6200, 592), (2, 2)),
+          ((225, 4128, 592), (3, 2)), ((333, 2992, 592), (3, 2)), ((700, 1504, 592), (3, 2)), ((161, 6200, 592), (3, 2)),
+          ((100, 8224, 784), (2, 3)), ((500, 2992, 784), (2, 3)), ((300, 4128, 1104), (2, 3)),
+          ((333, 4128, 1104), (4, 2)), ((200, 6200, 1040), (4, 2)), ((200, 6176, 1040), (4, 2))]
 
 
-@pytest.mark.parametrize("M,N,K", SHAPES)
-def test_short_gemm(M, N, K):
+def test_short_gemm_tiles():
+    """Every tile has a shape with ragged rows, and with an NVFP4 and a SwiGLU output."""
+    for tile in ((1, 1), (1, 2), (2, 2), (3, 2), (2, 3), (4, 2)):
+        mine = [s for s, t in SHAPES if t == tile]
+        assert any(N % 16 == 0 and M % 32 for M, N, K in mine) and any(N % 32 == 0 and M % 32 for M, N, K in mine)
+        assert any(N % (32 * tile[1]) for M, N, K in mine)
+
+
+@pytest.mark.parametrize("shape,tile", SHAPES)
+def test_short_gemm(shape, tile):
+    M, N, K = shape
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert cus != 256 or plans.gemm_short_tile(M, N, K, cus) == tile
     print("short gemm", M, N, K, flush=True)
     xb = synth.random_bf16(M + N, (M, K), outlier_frac=0.01, outlier_factor=20)
     w = synth.random_f32(N + K, (N, K), 0.02)
