@@ -594,9 +594,10 @@ __global__ __launch_bounds__(Gm::threads, Gm::occ) void nvfp4_gemm_kernel(
 // Measured beside it: deeper register rings (within 3 %), eight wavefronts
 // against four of the same tile (within 5 %), dequantizing a whole sub-step
 // ahead of its MFMAs instead of between them (5-15 % slower).
-template <int TM, int TN, int S, int RING>
+template <int TM, int TN, int S, int RING, int CONC>
 struct ShortGeo {
   static constexpr int tm = TM, tn = TN, waves = S;
+  static constexpr int conc = CONC;                        // workgroups per compute unit (by registers)
   static constexpr int blocks = TM * TN;
   static constexpr int rb = blocks < 4 ? blocks : 4;       // blocks reduced per round
   static constexpr size_t lds = (size_t)rb * S * 4096;
@@ -604,7 +605,7 @@ struct ShortGeo {
 };
 
 template <class Gm, int OUT, bool SW>
-__global__ __launch_bounds__(64 * Gm::waves, Gm::waves / 4) void nvfp4_gemm_short_kernel(
+__global__ __launch_bounds__(64 * Gm::waves, Gm::waves == 8 ? Gm::waves * Gm::conc / 4 : 1) void nvfp4_gemm_short_kernel(
     const uint8_t* __restrict__ a_codes, const uint8_t* __restrict__ a_scales, const float* __restrict__ Ga,
     const uint8_t* __restrict__ w_codes, const uint8_t* __restrict__ w_scales, const float* __restrict__ Gw,
     int64_t M, int a_tiles_r, int w_tiles_r, int KT, int tiles_m, int tiles_n, int SPW, GemmOut out) {
@@ -743,6 +744,14 @@ __global__ __launch_bounds__(64 * Gm::waves, Gm::waves / 4) void nvfp4_gemm_shor
         }
 #pragma unroll
         for (int t = 0; t < 4; ++t) sum[4 * g + t] = o[t];
+        // (Left to itself, the compiler sinks an NVFP4 block's sums into the
+        // branches that use them and so holds all 4 S reads at once: 138
+        // registers, one workgroup of eight per compute unit where the tile is
+        // chosen for two.  16 x 34816 x 5120 33.1 -> 28.8 us; pinned after
+        // every g, the small calls wait 0.3 us longer.)
+        if (OUT == kOutNvfp4 && S * Gm::conc == 16 && g == 1)
+          asm volatile("" : "+v"(sum[0]), "+v"(sum[1]), "+v"(sum[2]), "+v"(sum[3]), "+v"(sum[4]), "+v"(sum[5]),
+                            "+v"(sum[6]), "+v"(sum[7]));
       }
       store_block<OUT, SW>(sum, gs, m0 + (b / TN) * 32, n0 + (b % TN) * 32, lane, M, out);
     }
@@ -833,8 +842,8 @@ hipError_t launch_geo(const GemmArgs& a, int64_t split, hipStream_t s) {
 
 // The short-grid kernel's launchers, in the order of kShortFits
 hipError_t (*const kShortLaunch[kNumShortFits])(const GemmArgs&, hipStream_t) = {
-    launch_short<ShortGeo<1, 1, 8, 4>>, launch_short<ShortGeo<1, 2, 8, 4>>, launch_short<ShortGeo<2, 2, 8, 3>>,
-    launch_short<ShortGeo<3, 2, 4, 2>>, launch_short<ShortGeo<2, 3, 4, 2>>, launch_short<ShortGeo<4, 2, 8, 2>>};
+    launch_short<ShortGeo<1, 1, 8, 4, 2>>, launch_short<ShortGeo<1, 2, 8, 4, 2>>, launch_short<ShortGeo<2, 2, 8, 3, 1>>,
+    launch_short<ShortGeo<3, 2, 4, 2, 2>>, launch_short<ShortGeo<2, 3, 4, 2, 2>>, launch_short<ShortGeo<4, 2, 8, 2, 1>>};
 
 }  // namespace
 
