@@ -151,9 +151,11 @@ __device__ inline float swiglu(float g, float u) { return g / (1.0f + expf(-g)) 
 // 0..3, h = l/32).  With SwiGLU the weight rows come in gate/up groups of 16,
 // so registers 4g + t (g < 2, gate) and 4(g + 2) + t (up) of the same lane
 // meet, producing output feature nb/2 + 8g + 4h + t.  All 64 lanes take part.
+// Go: *out.G_out (NVFP4 output), read once by the caller: the stores between
+// blocks would make each block read it again and wait for it.
 template <int OUT, bool SW>
-__device__ __forceinline__ void store_block(const float16_t& acc, float gs, int64_t mb, int64_t nb, int lane, int64_t M,
-                                            const GemmOut& out) {
+__device__ __forceinline__ void store_block(const float16_t& acc, float gs, float Go, int64_t mb, int64_t nb, int lane,
+                                            int64_t M, const GemmOut& out) {
   const int h = lane >> 5;
   if constexpr (OUT != kOutNvfp4) {
     const bool vec = (out.Nout & 3) == 0;
@@ -196,7 +198,6 @@ __device__ __forceinline__ void store_block(const float16_t& acc, float gs, int6
     // a 16-column block of a row is held by lanes l and l ^ 32 (8 values
     // each), so the block maximum is one cross-lane step; each of the two
     // lanes stores one dword of 8 codes.
-    const float Go = *out.G_out;
     const float den = 6.0f * Go;
     const int64_t tr = mb / 32;
     if (tr >= out.tiles_r) return;
@@ -553,12 +554,14 @@ __device__ __forceinline__ void gemm_tile(
       return;
     }
   }
+  const float Go = OUT == kOutNvfp4 ? *out.G_out : 0.0f;
   if constexpr (OUT == kOutNvfp4)
-    if (blockIdx.x == 0 && threadIdx.x == 0 && out.G != out.G_out) *out.G = *out.G_out;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && out.G != out.G_out) *out.G = Go;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) store_block<OUT, SW>(acc[i][j], gs, m0 + i * 32, n0 + j * 32, lane, M, out);
+    for (int j = 0; j < TN; ++j)
+      store_block<OUT, SW>(acc[i][j], gs, Go, m0 + i * 32, n0 + j * 32, lane, M, out);
 }
 
 // One launch, two geometries: workgroups 0 .. big tiles - 1 take the tiles
@@ -717,8 +720,9 @@ __global__ __launch_bounds__(64 * Gm::waves, Gm::waves == 8 ? Gm::waves * Gm::co
   const float gs = (*Ga) * (*Gw);
   constexpr int RB = Gm::rb;
   float4_t* red = reinterpret_cast<float4_t*>(smem);
+  const float Go = OUT == kOutNvfp4 ? *out.G_out : 0.0f;
   if constexpr (OUT == kOutNvfp4)
-    if (blockIdx.x == 0 && threadIdx.x == 0 && out.G != out.G_out) *out.G = *out.G_out;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && out.G != out.G_out) *out.G = Go;
   static_for<0, (Gm::blocks + RB - 1) / RB>([&](auto rc) {
     constexpr int b0 = decltype(rc)::value * RB;
     if (b0 > 0) __syncthreads();   // the previous round has been read
@@ -753,7 +757,7 @@ __global__ __launch_bounds__(64 * Gm::waves, Gm::waves == 8 ? Gm::waves * Gm::co
           asm volatile("" : "+v"(sum[0]), "+v"(sum[1]), "+v"(sum[2]), "+v"(sum[3]), "+v"(sum[4]), "+v"(sum[5]),
                             "+v"(sum[6]), "+v"(sum[7]));
       }
-      store_block<OUT, SW>(sum, gs, m0 + (b / TN) * 32, n0 + (b % TN) * 32, lane, M, out);
+      store_block<OUT, SW>(sum, gs, Go, m0 + (b / TN) * 32, n0 + (b % TN) * 32, lane, M, out);
     }
   });
 }
