@@ -116,8 +116,9 @@ __device__ inline void store_group(uint8_t* codes, int64_t row, int64_t group, i
 //     row), goes to that bucket's list;
 //  3. a wavefront ranks each threshold in its bucket's list; a crowded bucket,
 //     of more than kCap members (few distinct values, extreme tails), is
-//     bisected instead, bit by bit over the keys below the common prefix of
-//     its members (none when they are all equal).  The values of these
+//     narrowed instead: a histogram of 128 parts of the key range that holds
+//     the threshold, all thresholds in one pass over the row, until one key is
+//     left (no pass when the members are all equal, at most 5).  The values of these
 //     buckets join the sums, which are merged in a fixed order.  Values equal to a threshold
 //     that belong below it are moved by count: bin j = class j + d_{j+1}
 //     T_{j+1} - d_j T_j, with d_j = j K / 2^b minus the number of values
@@ -127,10 +128,15 @@ __device__ inline void store_group(uint8_t* codes, int64_t row, int64_t group, i
 //     their four codes each into a 32-code group.
 // Bound: the VALU (about 78 instructions per value) and the LDS accesses
 // beside it; the row is read once.  A bitonic sort of the row in LDS (78
-// passes at K = 4096) took 1417 us for 12288 x 4096, this takes 157
-// (1.4 TB/s; 475 with weights of few distinct values).  Thresholds by
-// comparison for every value, four wavefronts per row instead of two and a
-// full double-double merge took 207.  The 16 rows of a tile run on one XCD, so that their 12-byte groups merge into whole lines in its L2.
+// passes at K = 4096) took 1417 us for 12288 x 4096, this takes 154
+// (1.4 TB/s).  Thresholds by comparison for every value, four wavefronts per
+// row instead of two and a full double-double merge took 207.  Crowded rows
+// (4096 x 4096, 3 bits; 461 sorted): a few distinct values 125 us, one outlier
+// of 10^8 265, many octaves 255.  Bisecting each threshold by itself, bit by
+// bit, took 185, 732 and 538; sixteen such rows, where a round's latency is
+// all, took 155 and 123 us and now take 58 and 70 (49 sorted).  The 16 rows of
+// a tile run on one XCD, so that their 12-byte groups merge into whole lines
+// in its L2.
 constexpr int kBuckets = 2048;
 constexpr int kCap = 128;   // members of a threshold's bucket that are listed and ranked
 
@@ -146,6 +152,13 @@ __device__ inline float f64_to_f32_down(double d) {
   if (!((double)f > d)) return f;
   const uint32_t b = __float_as_uint(f);
   return __uint_as_float((b & 0x7FFFFFFFu) == 0u ? 0x80000001u : (b & 0x80000000u) ? b + 1u : b - 1u);
+}
+
+// 0 .. span in kCap equal parts or fewer: the part of x is x >> digit_shift
+__device__ inline int digit_shift(uint32_t span) {
+  constexpr int digit = 31 - __builtin_clz(kCap);
+  static_assert(kCap == 1 << digit && kCap == 128, "two parts per lane");
+  return max(0, 32 - digit - __builtin_clz(span | 1u));
 }
 
 // #{j : x > m[j]}, m ascending
@@ -179,7 +192,8 @@ __global__ __launch_bounds__(T) void pack_lut_per_row_kernel(const float* __rest
   __shared__ float s_f[NW];
   __shared__ uint32_t s_w[2][NW];
   __shared__ int s_slot[NT], s_lo[NT], s_cnt[NT], s_fill[NT], s_less[NT];
-  __shared__ uint32_t s_key[NT], s_min[NT], s_max[NT];
+  __shared__ uint4 s_range[NT + 1];
+  __shared__ uint32_t s_key[NT], s_span[NT], s_min[NT], s_max[NT];
   __shared__ double s_hi[NB], s_lo2[NB];
   __shared__ uint16_t s_entry[NB];
 
@@ -225,7 +239,7 @@ __global__ __launch_bounds__(T) void pack_lut_per_row_kernel(const float* __rest
   if (tid < NT) {
     s_slot[tid] = s_lo[tid] = s_less[tid] = 0;
     s_cnt[tid] = s_fill[tid] = 0;
-    s_key[tid] = s_max[tid] = 0u;
+    s_key[tid] = s_span[tid] = s_max[tid] = 0u;
     s_min[tid] = 0xFFFFFFFFu;
   }
   __syncthreads();
@@ -330,35 +344,71 @@ __global__ __launch_bounds__(T) void pack_lut_per_row_kernel(const float* __rest
     }
   }
   if (!listed) {
-    for (int j = 0; j < NT; ++j) {
-      if (s_cnt[j] <= kCap) continue;   // uniform over the workgroup
-      // the largest key with at most (j + 1) cnt keys below it, from the
-      // common prefix of the bucket's members down
-      const uint32_t differ = s_min[s_slot[j]] ^ s_max[s_slot[j]];
-      const int bits = differ == 0u ? 0 : 32 - __clz((int)differ);
-      uint32_t key = bits == 32 ? 0u : s_min[s_slot[j]] >> bits << bits;
-      int less = s_lo[j];
-      for (int bit = bits - 1; bit >= 0; --bit) {
-        const uint32_t trial = key | (1u << bit);
-        uint32_t below = 0;
+    // the range base .. base + span of keys of the bucket that holds threshold j
+    if (tid < NT && s_cnt[tid] > kCap) {
+      s_key[tid] = s_min[s_slot[tid]];
+      s_span[tid] = s_max[s_slot[tid]] - s_key[tid];
+    }
+    __syncthreads();
+    for (int round = 0; round < 5; ++round) {   // each leaves 7 bits less of the ranges
+      // the distinct ranges in ascending order (equal bases: equal ranges; two
+      // that differ have no key in common), each with a row of counts
+      uint32_t base[NT], rows = 0u;
+      int n = 0;
 #pragma unroll
-        for (int e = 0; e < E4; ++e)
-#pragma unroll
-          for (int t = 0; t < 4; ++t)
-            below += (uint32_t)__popcll(__ballot(tid + e * T < nq && sort_key(v[e][t]) < trial));
-        if (lane == 0) s_w[bit & 1][wave] = below;
-        __syncthreads();
-        below = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) below += s_w[bit & 1][w];
-        if ((int)below <= (j + 1) * cnt) {
-          key = trial;
-          less = (int)below;
+      for (int j = 0; j < NT; ++j) {
+        const uint32_t b = s_key[j], span = s_span[j];
+        base[j] = 0xFFFFFFFFu;
+        if (span != 0u && (n == 0 || b != s_key[j - 1] || s_span[j - 1] == 0u)) {
+          if (tid == 0) s_range[n + 1] = uint4{b, span, (uint32_t)digit_shift(span), (uint32_t)j};
+          ++n;
+          rows |= 1u << j;
+          if (tid < kCap) s_cand[j][tid] = 0u;
         }
       }
-      if (tid == 0) {
-        s_key[j] = key;
-        s_less[j] = less;
+      if (n == 0) break;
+      if (tid == 0) s_range[0] = uint4{0xFFFFFFFFu, 0u, 0u, 0u};   // keys below the first: none
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        if (j < n) base[j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_range[j + 1].x);
+#pragma unroll
+      for (int e = 0; e < E4; ++e) {
+        if (tid + e * T < nq)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            float x = v[e][t];
+            asm volatile("" : "+v"(x));   // the keys of the row are not kept from round to round: registers
+            const uint32_t key = sort_key(x);
+            int i = 0;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) i += key >= base[j] ? 1 : 0;
+            const uint4 r = s_range[min(i, n)];
+            if (key - r.x <= r.y) atomicAdd(&s_cand[r.w][(key - r.x) >> r.z], 1u);
+          }
+        __builtin_amdgcn_sched_barrier(0);   // no table entries in flight for the next quad either
+      }
+      __syncthreads();
+      for (int j = wave; j < NT; j += NW) {
+        const uint32_t from = s_key[j], span = s_span[j];
+        if (span == 0u) continue;
+        const int row_of = 31 - __clz((int)(rows & ((2u << j) - 1u)));
+        const uint32_t h0 = s_cand[row_of][2 * lane], h1 = s_cand[row_of][2 * lane + 1];
+        uint32_t hi = h0 + h1;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const uint32_t o = (uint32_t)__shfl_up((int)hi, off, 64);
+          if (lane >= off) hi += o;
+        }
+        const uint32_t lo = hi - h0 - h1, rank = (uint32_t)((j + 1) * cnt - s_less[j]);
+        if (lo <= rank && rank < hi) {   // one lane
+          const bool second = rank >= lo + h0;
+          const int shift = digit_shift(span);
+          const uint32_t to = from + ((uint32_t)(2 * lane + (second ? 1 : 0)) << shift);
+          s_key[j] = to;
+          s_span[j] = min((1u << shift) - 1u, from + span - to);
+          s_less[j] += (int)(lo + (second ? h0 : 0u));
+        }
       }
       __syncthreads();
     }

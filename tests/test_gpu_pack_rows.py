@@ -1,7 +1,7 @@
 """Per-row LUT packing at the edges of its selection: rows whose bin
-boundaries fall on ties, whose values crowd one histogram bucket (bisection)
-or spread over the whole fp32 range, and row lengths at the ends of every
-kernel's range.  Codes and entries equal the oracle's, bit for bit."""
+boundaries fall on ties, whose values crowd one histogram bucket (narrowed by
+finer histograms) or spread over the whole fp32 range, and row lengths at the
+ends of every kernel's range.  Codes and entries equal the oracle's, bit for bit."""
 import os
 import sys
 
@@ -67,6 +67,40 @@ def test_pack_lut_rows(K, bits):
     full = L.lut_codes_unpack(raw, (N + 15) // 16 * 16, (K + 127) // 128 * 128, bits)
     assert np.array_equal(full[:N, :K], codes)
     assert not full[N:].any() and not full[:, K:].any()
+
+
+def crowded_rows(K):
+    """Rows whose thresholds share crowded buckets, part after some of the
+    rounds that narrow them, and end on keys one apart, equal, or far apart."""
+    rng = np.random.default_rng([13, K])
+    z = rng.standard_normal(K, dtype=np.float32)
+    far = np.arange(K) == K - 1   # widens the buckets: the others fall into one or two
+
+    def ulps(start, n):   # n neighbouring floats, over and over
+        return (np.float32(start).view(np.int32) + rng.integers(0, n, K).astype(np.int32)).view(np.float32)
+
+    out = [np.where(far, 50.0 * K, z),                           # both signs, each in one bucket
+           np.where(far, -50.0 * K, np.abs(z)),                  # the positive one alone
+           np.where(far, 50.0 * K, ulps(1.0, 7)), np.where(far, 50.0 * K, ulps(-1.0, 200)),   # keys one apart
+           np.where(far, 50.0 * K, ulps(1.0, 128 * 128)), np.where(far, 50.0 * K, ulps(0.9, 128 * 128 + 1)),
+           np.where(far, 50.0 * K, np.where(z > 0, ulps(3.0, 3), ulps(-1e-20, 1000))),   # two far clusters
+           np.where(far, 50.0 * K, np.where(z > 0.3, 1.0, z)),   # a tie beside single keys
+           np.exp2(rng.uniform(-140.0, 14.0, K)) * np.sign(z),   # every octave, both signs
+           np.where(far, 50.0 * K, np.exp2(rng.uniform(-140.0, 3.0, K)))]
+    return np.stack(out).astype(np.float32)
+
+
+@pytest.mark.parametrize("K", [1024, 2048, 4096, 5120, 8192, 12288, 16896, 20480, 32768])   # one per kernel
+@pytest.mark.parametrize("bits", [3, 2])
+def test_pack_lut_rows_crowded(K, bits):
+    print("pack crowded rows", K, bits, flush=True)
+    w = crowded_rows(K)
+    codes, table = lut.quantize_per_row(w, bits)
+    assert np.isfinite(table).all()
+    Wq = dq.dq_pack_lut3(torch.from_numpy(w).cuda(), bits=bits, mode=dq.LUT_PER_ROW)
+    torch.cuda.synchronize()
+    assert np.array_equal(Wq.lut.cpu().numpy().view(np.uint16).reshape(-1, 1 << bits)[:len(w)], table.view(np.uint16))
+    assert np.array_equal(L.lut_codes_unpack(Wq.codes.cpu().numpy(), len(w), K, bits), codes)
 
 
 def test_pack_lut_rows_many_tiles():
