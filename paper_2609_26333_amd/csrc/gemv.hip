@@ -366,8 +366,8 @@ __device__ inline void reduce_store(float4_t acc, float4_t* red, int wave, int l
 
 
 // ---------------------------------------------------------------- persistent
-// Resident workgroups that loop over row tiles (used whenever the staged
-// activations fit in LDS).  Workgroup g owns the R consecutive row tiles
+// Batch 1: resident workgroups that loop over row tiles (used whenever the
+// staged activations fit in LDS).  Workgroup g owns the R consecutive row tiles
 // g*R .. g*R + R - 1 ("rounds"; the last workgroup may have fewer); its W
 // wavefronts split every tile's K: wavefront w consumes
 // chunks w, w + W, ... of the tile (CPW = ceil(KC / W) slots per round).
@@ -400,7 +400,7 @@ __device__ inline float wave_max_dpp(float v) {
 
 template <int BITS, int MODE, int RING, int XREG, int TI>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6)))
-void lut_gemv_persist_kernel(const uint16_t* __restrict__ x, int B, int64_t K, const uint8_t* __restrict__ codes,
+void lut_gemv_persist_kernel(const uint16_t* __restrict__ x, int64_t K, const uint8_t* __restrict__ codes,
                              const uint16_t* __restrict__ lut, const uint8_t* __restrict__ scales,
                              const float* __restrict__ Gp, int64_t N, PersistPlan plan, int out_kind,
                              void* __restrict__ y) {
@@ -420,21 +420,20 @@ void lut_gemv_persist_kernel(const uint16_t* __restrict__ x, int B, int64_t K, c
   const int T = (int)plan.tiles;
   const int t0 = (int)blockIdx.x * R;              // this workgroup's tiles: t0 .. t0 + nr - 1
   const int nr = min(R, T - t0);                   // rounds of this workgroup (1 <= nr <= R)
-  const int rowstride = (KCi + 1) * 128 + 8;       // fp16 per staged batch row (+ zero chunk, pad)
   // LDS: staged activations | partial sums [R][W][64] float4 | tables [W][TI KiB] (PER_ROW)
   _Float16* xs = reinterpret_cast<_Float16*>(smem);
-  float4_t* part = reinterpret_cast<float4_t*>(smem + (size_t)B * rowstride * 2);
+  float4_t* part = reinterpret_cast<float4_t*>(smem + (size_t)(KCi + 1) * 256 + 16);   // past the zero chunk, padded
   uint8_t* tabs = reinterpret_cast<uint8_t*>(part + (size_t)R * W * 64) + (size_t)wave * TI * 1024;
-  const int i = lane & 15, j = lane & 15, q = lane >> 4;
+  const int i = lane & 15, q = lane >> 4;
   auto tile_of = [&](int r) { return t0 + r; };
 
   // ---- 1. this wavefront's activation chunks (lane l: elements 2l, 2l+1 of
-  // each chunk), and the tables of its rounds.  Batch 1 with at most XREG
-  // chunks per wavefront: into registers through a range-checked buffer
-  // resource (reads past K return zero).  Otherwise raw into LDS, with reads
-  // past K clamped in bounds and zeroed at conversion.
+  // each chunk), and the tables of its rounds.  With at most XREG chunks per
+  // wavefront: into registers through a range-checked buffer resource (reads
+  // past K return zero).  Otherwise raw into LDS, with reads past K clamped in
+  // bounds and zeroed at conversion.
   const int nxc = (KCi - wave + W - 1) / W;        // chunks of this wavefront
-  constexpr bool xreg = XREG > 0;   // the host guarantees B == 1 and nxc <= XREG
+  constexpr bool xreg = XREG > 0;   // the host guarantees nxc <= XREG
   uint32_t xr[XREG > 0 ? XREG : 1];
   if constexpr (xreg) {
     const i32x4_t rx = buffer_resource(x, (uint32_t)(K * 2));
@@ -442,12 +441,11 @@ void lut_gemv_persist_kernel(const uint16_t* __restrict__ x, int B, int64_t K, c
     for (int u = 0; u < (XREG > 0 ? XREG : 1); ++u)
       xr[u] = (uint32_t)raw_buffer_load_b32(rx, lane * 4 + ((u * W + wave) * 128) * 2, 0, 0);
   } else {
-    for (int jj = 0; jj < B; ++jj)
-      for (int c = wave; c < KCi; c += W) {
-        const int64_t k = min((int64_t)c * 128 + 2 * lane, K - 2);
-        __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(x + (int64_t)jj * K + k),
-                                         reinterpret_cast<void*>(xs + jj * rowstride + c * 128), 4, 0, 0);
-      }
+    for (int c = wave; c < KCi; c += W) {
+      const int64_t k = min((int64_t)c * 128 + 2 * lane, K - 2);
+      __builtin_amdgcn_global_load_lds(reinterpret_cast<const void*>(x + k), reinterpret_cast<void*>(xs + c * 128), 4,
+                                       0, 0);
+    }
   }
   if (MODE == 0) {
     // the tables of tiles t0 .. are contiguous: TI KiB per wavefront (a fixed
@@ -496,8 +494,8 @@ void lut_gemv_persist_kernel(const uint16_t* __restrict__ x, int B, int64_t K, c
 #pragma unroll
   for (int r = 0; r < RING; ++r) load_next(r);
   __builtin_amdgcn_sched_barrier(0);
-  // the zero chunk of every staged row (each wavefront writes the same zeros)
-  for (int jj = 0; jj < B; ++jj) reinterpret_cast<uint32_t*>(xs + jj * rowstride + KCi * 128)[lane] = 0u;
+  // the zero chunk (each wavefront writes the same zeros)
+  reinterpret_cast<uint32_t*>(xs + KCi * 128)[lane] = 0u;
 
   // ---- 3. once its own loads have landed (vmcnt: the code loads may still
   // be in flight), the wavefront rescales and converts its chunks in place
@@ -514,6 +512,7 @@ void lut_gemv_persist_kernel(const uint16_t* __restrict__ x, int B, int64_t K, c
   auto to_h2 = [](uint32_t v, float sc) {
     return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(bf16_lo(v) * sc, bf16_hi(v) * sc));
   };
+  uint32_t* row = reinterpret_cast<uint32_t*>(xs) + lane;
   if constexpr (xreg) {
     float m = 0.0f;
 #pragma unroll
@@ -522,38 +521,33 @@ void lut_gemv_persist_kernel(const uint16_t* __restrict__ x, int B, int64_t K, c
     const int e = stage_exponent(__float_as_uint(wave_max_dpp(m)));
     const float sc = __builtin_ldexpf(1.0f, e);
     unscale = __builtin_ldexpf(1.0f, -e);
-    uint32_t* row = reinterpret_cast<uint32_t*>(xs) + lane;
 #pragma unroll
     for (int u = 0; u < (XREG > 0 ? XREG : 1); ++u)
       if (u < nxc) row[(u * W + wave) * 64] = to_h2(xr[u], sc);
   } else {
     // batches of 8 chunks, so that the LDS round trips overlap
-    for (int jj = 0; jj < B; ++jj) {
-      uint32_t* row = reinterpret_cast<uint32_t*>(xs + jj * rowstride) + lane;
-      float m = 0.0f;
-      for (int t0 = 0; t0 < nxc; t0 += 8) {
-        uint32_t v[8];
+    float m = 0.0f;
+    for (int t0 = 0; t0 < nxc; t0 += 8) {
+      uint32_t v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = t0 + u < nxc ? row[((t0 + u) * W + wave) * 64] : 0u;
+      for (int u = 0; u < 8; ++u) v[u] = t0 + u < nxc ? row[((t0 + u) * W + wave) * 64] : 0u;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) m = fmaxf(m, fmaxf(fabsf(bf16_lo(v[u])), fabsf(bf16_hi(v[u]))));
-      }
-      const int e = stage_exponent(__float_as_uint(wave_max_dpp(m)));
-      const float sc = __builtin_ldexpf(1.0f, e);
-      if (j == jj) unscale = __builtin_ldexpf(1.0f, -e);
-      for (int t0 = 0; t0 < nxc; t0 += 8) {
-        uint32_t v[8];
+      for (int u = 0; u < 8; ++u) m = fmaxf(m, fmaxf(fabsf(bf16_lo(v[u])), fabsf(bf16_hi(v[u]))));
+    }
+    const int e = stage_exponent(__float_as_uint(wave_max_dpp(m)));
+    const float sc = __builtin_ldexpf(1.0f, e);
+    unscale = __builtin_ldexpf(1.0f, -e);
+    for (int t0 = 0; t0 < nxc; t0 += 8) {
+      uint32_t v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = t0 + u < nxc ? row[((t0 + u) * W + wave) * 64] : 0u;
+      for (int u = 0; u < 8; ++u) v[u] = t0 + u < nxc ? row[((t0 + u) * W + wave) * 64] : 0u;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int c = (t0 + u) * W + wave;
-          if (t0 + u < nxc) row[c * 64] = (int64_t)c * 128 + 2 * lane < K ? to_h2(v[u], sc) : 0u;
-        }
+      for (int u = 0; u < 8; ++u) {
+        const int c = (t0 + u) * W + wave;
+        if (t0 + u < nxc) row[c * 64] = (int64_t)c * 128 + 2 * lane < K ? to_h2(v[u], sc) : 0u;
       }
     }
   }
-  const bool xlane = j < B;
   if (MODE == 1) unscale *= *Gp;
   auto round_table = [&](int r) {
     if (MODE == 1) return grid_tab;
@@ -576,8 +570,8 @@ void lut_gemv_persist_kernel(const uint16_t* __restrict__ x, int B, int64_t K, c
   float4_t pacc[4];
 #pragma unroll
   for (int st = 0; st < 4; ++st) pacc[st] = float4_t{0.f, 0.f, 0.f, 0.f};
-  // batch columns >= B read row 0: their MFMA output columns are never stored
-  const _Float16* xrow = xs + (xlane ? j : 0) * rowstride + 32 * q;
+  // every batch column of the MFMAs reads x; column 0 is stored
+  const _Float16* xrow = xs + 32 * q;
   const int total = nr * CPW;
   int rd = 0, s = 0;   // consume cursor
   // slot r of the ring (r is a compile-time index once inlined)
@@ -654,7 +648,7 @@ void lut_gemv_persist_kernel(const uint16_t* __restrict__ x, int B, int64_t K, c
   // ---- 5. reduce each round's W partials in order and store the tile
   __syncthreads();
   for (int r = wave; r < nr; r += W) {
-    if (!xlane) continue;
+    if (i != 0) continue;
     const float4_t* pr = part + (size_t)r * W * 64 + lane;
     float4_t o = pr[0];
     for (int w2 = 1; w2 < W; ++w2) {
@@ -669,11 +663,10 @@ void lut_gemv_persist_kernel(const uint16_t* __restrict__ x, int B, int64_t K, c
     for (int r2 = 0; r2 < 4; ++r2) {
       const int64_t row = tile * 16 + 4 * q + r2;
       if (row < N) {
-        const int64_t o2 = (int64_t)j * N + row;
         if (out_kind == 0)
-          reinterpret_cast<float*>(y)[o2] = o[r2];
+          reinterpret_cast<float*>(y)[row] = o[r2];
         else
-          reinterpret_cast<uint16_t*>(y)[o2] = (uint16_t)f32_to_bf16_rne(o[r2]);
+          reinterpret_cast<uint16_t*>(y)[row] = (uint16_t)f32_to_bf16_rne(o[r2]);
       }
     }
   }
@@ -1245,14 +1238,14 @@ hipError_t launch_gemv_t(const uint16_t* x, int64_t B, const LutView& w, int out
     constexpr int kTabBytes = 32 << BITS;
     const int64_t code_bytes = pl.tiles * pl.KC * 64 * (BITS == 3 ? 12 : 8);
     const int64_t cpw = (pl.KC + kW - 1) / kW;
-    const int xv = B == 1 && cpw <= 8 ? 0 : B == 1 && cpw <= 18 ? 1 : 2;   // activation staging variant
+    const int xv = cpw <= 8 ? 0 : cpw <= 18 ? 1 : 2;   // activation staging variant
     auto table_kib = [&](int64_t rounds) { return (rounds * kTabBytes + 1023) / 1024; };
     // LDS: staged activations, per round W partial sums, W table copies
     auto lds_of = [&](int64_t rounds) {
-      return B * ((pl.KC + 1) * 128 + 8) * 2 + rounds * kW * 1024 + (MODE == 0 ? kW * table_kib(rounds) * 1024 : 0);
+      return (pl.KC + 1) * 256 + 16 + rounds * kW * 1024 + (MODE == 0 ? kW * table_kib(rounds) * 1024 : 0);
     };
-    typedef void (*kern_t)(const uint16_t*, int, int64_t, const uint8_t*, const uint16_t*, const uint8_t*,
-                           const float*, int64_t, PersistPlan, int, void*);
+    typedef void (*kern_t)(const uint16_t*, int64_t, const uint8_t*, const uint16_t*, const uint8_t*, const float*,
+                           int64_t, PersistPlan, int, void*);
     auto pick = [&](int ti) -> kern_t {
       if (ti <= 1)
         return xv == 0 ? lut_gemv_persist_kernel<BITS, MODE, kRingPersist, 8, 1>
@@ -1293,13 +1286,12 @@ hipError_t launch_gemv_t(const uint16_t* x, int64_t B, const LutView& w, int out
         pp.CPW = (int)cpw;
         pp.rounds = (int)rounds;
         const int64_t G = (pl.tiles + rounds - 1) / rounds;
-        hipLaunchKernelGGL(pick(ti), dim3((unsigned)G), dim3(kW * 64), (size_t)lds_of(rounds), s, x, (int)B, K,
-                           w.codes, w.lut, w.scales, w.G, N, pp, out_kind, y);
+        hipLaunchKernelGGL(pick(ti), dim3((unsigned)G), dim3(kW * 64), (size_t)lds_of(rounds), s, x, K, w.codes,
+                           w.lut, w.scales, w.G, N, pp, out_kind, y);
         return hipGetLastError();
       }
     }
   }
-pieces:
   // Several pieces.  Row tiles per workgroup: the workgroups must spread
   // evenly over the compute units (cost = rounds x row tiles per workgroup);
   // ties go to more row tiles per workgroup, which amortizes the staging.  K
