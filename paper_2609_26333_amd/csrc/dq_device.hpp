@@ -1,7 +1,7 @@
 // Device helpers shared by the gfx950 kernels: operand vector types, a
-// compile-time loop, the E4M3 / E2M1 encoders used by the NVFP4 quantizers,
-// exact fp32 division by a block scale, and the tiled NVFP4 / LUT layout
-// offsets declared in dq.h.
+// compile-time loop, the E2M1 decoder of the GEMV and GEMM kernels, the E4M3 /
+// E2M1 encoders used by the NVFP4 quantizers, exact fp32 division by a block
+// scale, and the tiled NVFP4 / LUT layout offsets declared in dq.h.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -35,6 +35,16 @@ __device__ __forceinline__ void static_for(F&& f) {
 // ---------------------------------------------------------------- layouts
 // NVFP4 "32x64 tiles" (see dq.h).
 __host__ __device__ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
+
+// ---------------------------------------------------------------- E2M1
+// 8 E2M1 codes (one dword) times an fp16 block scale -> 8 exact fp16 values
+__device__ inline half8_t e2m1_times(uint32_t w, half2_t s) {
+  const half2_t p0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 0) * s;
+  const half2_t p1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 1) * s;
+  const half2_t p2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 2) * s;
+  const half2_t p3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 3) * s;
+  return half8_t{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
+}
 
 // ---------------------------------------------------------------- E4M3
 // Encode a non-negative fp32 value as OCP E4M3 (bias 7, max 448 = 0x7E):

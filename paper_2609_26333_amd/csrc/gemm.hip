@@ -82,16 +82,7 @@ struct Geo {
   static_assert(stages >= 4 && (stages - 1) * loads_per_wave <= 63, "LDS ring of four to six stages");
 };
 
-// 8 E2M1 codes (one dword) times an fp16 block scale -> 8 exact fp16 values.
-__device__ inline half8_t dequant8(uint32_t w, half2_t s) {
-  half2_t p0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 0) * s;
-  half2_t p1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 1) * s;
-  half2_t p2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 2) * s;
-  half2_t p3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 3) * s;
-  return half8_t{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
-}
-
-// Half of dequant8: values 4*HF .. 4*HF+3 of the dword into v
+// Half of e2m1_times: values 4*HF .. 4*HF+3 of the dword into v
 template <int HF>
 __device__ inline void dequant4(uint32_t w, half2_t s, half8_t& v) {
   const half2_t p0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 2 * HF) * s;
@@ -394,8 +385,8 @@ __device__ __forceinline__ void gemm_tile(
   };
   // sub-step s of tile u (A tiles first): dword s of the codes, scale byte s/2
   auto dequant_one = [&](const Raw& R, int s, Ops& D, int u) {
-    if (u < TM) D.a[u] = dequant8(R.a[u][s], scale_pair(R.sa[u], s >> 1));
-    else D.w[u - TM] = dequant8(R.w[u - TM][s], scale_pair(R.sw[u - TM], s >> 1));
+    if (u < TM) D.a[u] = e2m1_times(R.a[u][s], scale_pair(R.sa[u], s >> 1));
+    else D.w[u - TM] = e2m1_times(R.w[u - TM][s], scale_pair(R.sw[u - TM], s >> 1));
   };
   // the same in two halves, issued after different MFMAs (tile u's scale
   // pair kept in sp[u] between them)

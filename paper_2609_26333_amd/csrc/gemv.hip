@@ -73,15 +73,6 @@ struct CodeVec<4> {
   static constexpr int bytes = 16;
 };
 
-// 8 E2M1 codes times an fp16 block scale: 8 exact fp16 values
-__device__ inline half8_t e2m1_scaled8(uint32_t w, half2_t s) {
-  const half2_t p0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 0) * s;
-  const half2_t p1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 1) * s;
-  const half2_t p2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 2) * s;
-  const half2_t p3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 3) * s;
-  return half8_t{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
-}
-
 // fp16 pair from the low-byte and high-byte lookups of four codes
 __device__ inline void lookup4(uint32_t sel, uint32_t tl0, uint32_t tl1, uint32_t th0, uint32_t th1,
                                uint32_t& p0, uint32_t& p1) {
@@ -895,7 +886,7 @@ __global__ __launch_bounds__(1024) void lut_gemv_batch_kernel(
           __builtin_amdgcn_sched_barrier(0);   // one sub-step's operands at a time (registers)
           half8_t af;
           if constexpr (MODE == 2) {
-            af = e2m1_scaled8(ring[r][u].w[st], st < 2 ? s_lo : s_hi);
+            af = e2m1_times(ring[r][u].w[st], st < 2 ? s_lo : s_hi);
           } else {
             uint32_t a0, a1, a2, a3;
             lookup4(sel[2 * st], tl0, tl1, th0, th1, a0, a1);

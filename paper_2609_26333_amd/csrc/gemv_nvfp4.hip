@@ -51,15 +51,6 @@ __device__ inline v4i_t nv_resource(const void* p, uint32_t bytes) {
   return v4i_t{(int32_t)(uint32_t)a, (int32_t)(uint32_t)((a >> 32) & 0xFFFFu), (int32_t)bytes, 0x00020000};
 }
 
-// 8 E2M1 codes times an fp16 block scale -> 8 exact fp16 values
-__device__ inline half8_t nv_dequant8(uint32_t w, half2_t s) {
-  const half2_t p0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 0) * s;
-  const half2_t p1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 1) * s;
-  const half2_t p2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 2) * s;
-  const half2_t p3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 3) * s;
-  return half8_t{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
-}
-
 // fp16 rescale exponent of a batch row whose maximum magnitude has bits mb:
 // the maximum lands in [2^14, 2^15)
 __device__ inline int nv_stage_exponent(uint32_t mb) {
@@ -207,7 +198,7 @@ __global__ __launch_bounds__(256) void nvfp4_gemv_kernel(const uint16_t* __restr
       for (int s = 0; s < 4; ++s) xb[s] = *reinterpret_cast<const half8_t*>(xl + (st0 + u) * 64 + 8 * s);
 #pragma unroll
       for (int s = 0; s < 4; ++s)
-        acc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(nv_dequant8(cb.c[u][s], s < 2 ? s_lo : s_hi), xb[s],
+        acc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(e2m1_times(cb.c[u][s], s < 2 ? s_lo : s_hi), xb[s],
                                                             acc[s & 1], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -358,7 +349,7 @@ __global__ __launch_bounds__(64 * kKsWaves) void nvfp4_gemv_ks_kernel(
       for (int s = 0; s < 4; ++s) xb[s] = *reinterpret_cast<const half8_t*>(xl + st * 64 + 8 * s);
 #pragma unroll
       for (int s = 0; s < 4; ++s)
-        acc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(nv_dequant8(cb.c[u][s], s < 2 ? s_lo : s_hi), xb[s],
+        acc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(e2m1_times(cb.c[u][s], s < 2 ? s_lo : s_hi), xb[s],
                                                             acc[s & 1], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
