@@ -16,8 +16,8 @@
 //
 // Three kernels: the batched kernel of gemv.hip (activations in registers) for
 // all but two ranges, nvfp4_gemv_ks_kernel for small batches where it is still
-// the faster (see ks_better), and nvfp4_gemv_kernel for rows so wide that they
-// exceed the batched kernel's 32-bit offsets.
+// the faster (see ks_better), and nvfp4_gemv_kernel for rows so wide (from 2^25
+// columns) that they exceed the batched kernel's 32-bit offsets.
 //
 // nvfp4_gemv_kernel: a workgroup takes one K group of a group of row tiles,
 // stages that K slice of x once, and its wavefronts each stream whole tiles
@@ -538,7 +538,9 @@ hipError_t launch_gemv_nvfp4(const uint16_t* x, int64_t B, const NvFp4View& w, i
   }
   typedef void (*kern_t)(const uint16_t*, int, int64_t, const uint8_t*, const uint8_t*, const float*, int64_t, int,
                          int, int, int, float*, int, void*);
-  const kern_t kern = p.KC8 == 4 ? nvfp4_gemv_kernel<4> : p.KC8 == 2 ? nvfp4_gemv_kernel<2> : nvfp4_gemv_kernel<1>;
+  // 2^19 K steps or more, at most 4096 groups wanted: KC8 is what the LDS slice
+  // allows, 4 up to batch 11 and 2 beyond
+  const kern_t kern = p.KC8 == 4 ? nvfp4_gemv_kernel<4> : nvfp4_gemv_kernel<2>;
   hipLaunchKernelGGL(kern, dim3((unsigned)p.G), dim3(64 * kNvWaves), p.lds, s, x, (int)B, K, w.codes, w.scales,
                      w.G, N, p.T, p.KT, p.KG, p.TPW, p.KG > 1 ? partials : nullptr, out_kind, y);
   e = hipGetLastError();

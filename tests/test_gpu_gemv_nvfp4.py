@@ -104,6 +104,33 @@ def test_gemv_nvfp4_many_tiles(N, K, B, groups):
     check(w, xb, rows[rows < N])
 
 
+@pytest.mark.parametrize("N,B", [(3, 2), (2, 11), (2, 12), (1, 16)])
+def test_gemv_nvfp4_widest_rows(N, B):
+    """Rows past the batched kernel's offsets (2^25 columns): the K-group kernel,
+    two widths of the group.  x is zero but for a few scale blocks (the first,
+    the last, both sides of group edges and of 2^24), the weights are not."""
+    print("nvfp4 gemv widest rows", N, B, flush=True)
+    K = (1 << 25) + 16
+    assert not plans.gemv_plan(4, B, N, K, most=1).ok
+    at = [0, 1008, 1024, 2032, 2048, (1 << 24) - 16, 1 << 24, (1 << 25) - 16, 1 << 25]
+    cols = np.concatenate([np.arange(k, k + 16) for k in at])
+    on = torch.from_numpy(cols).cuda()
+    g = torch.Generator(device="cuda").manual_seed(N)
+    w = torch.randn((N, K), generator=g, device="cuda").mul_(0.02)
+    xb = synth.random_bf16(B, (B, len(cols)), outlier_frac=0.02, outlier_factor=30)
+    x = torch.zeros((B, K), dtype=torch.int16, device="cuda")
+    x[:, on] = dev(xb.view(np.int16))
+    Wq = dq.dq_pack_nvfp4(w)
+    y = dq.dq_decode_gemv_nvfp4(x, Wq, out_kind=dq.OUT_F32)
+    yb = dq.dq_decode_gemv_nvfp4(x, Wq, out_kind=dq.OUT_BF16)
+    torch.cuda.synchronize()
+    assert torch.equal(yb, y.bfloat16())
+    G = nvfp4.global_scale(np.float32(w.abs().max().item()))
+    q, c = nvfp4.quantize(w[:, on].cpu().numpy(), G)
+    bound = PB.gemv_bound(formats.f64_from_bf16_bits(xb), nvfp4.dequantize(q, c, G), len(cols))
+    PB.assert_within(y.cpu().numpy(), linalg.nvfp4a16_gemv(xb, q, c, G), bound, "nvfp4 gemv, widest rows")
+
+
 def test_gemv_nvfp4_scales_per_row():
     """Batch rows of very different magnitudes: each keeps its own scale."""
     N, K, B = 48, 4096, 16

@@ -494,10 +494,8 @@ def test_gemv_workspace_and_pool_paths_agree():
 
 
 # ---------------------------------------------------------------- NVFP4A16 decode GEMV
-# one-launch kernel (four wavefronts per row tile up to 64 K steps, else
-# eight): batch <= 8 with the activation slices in LDS and at most one
-# resident round of row tiles; the K-group kernel otherwise ((5120, 5120, 16),
-# (64, 4096, 8), (34816, 2048, 1))
+# the batched kernel and the one-launch kernel (batches to 4 at an even count of
+# row tiles per compute unit and a few other sizes), small, ragged and whole
 NV_GEMV_CASES = [(512, 512, 1), (100, 96, 3), (33, 1040, 2), (7168, 5120, 1), (5120, 17408, 1), (5120, 5120, 16),
                  (12288, 4096, 4), (64, 4096, 8), (17408, 2048, 1), (34816, 2048, 1), (16384, 208, 8), (40, 16, 1)]
 
