@@ -180,10 +180,11 @@ dq_status dq_pack_nvfp4(const float* W, int64_t N, int64_t K, const float* G_ove
 
 /* ---- a5: weight packing, LUT (bits 3 = LUT3, bits 2 = LUT2) --------------
  * W: device fp32 [N, K] row-major, K % 32 == 0.
- * PER_ROW: each row is sorted, cut into 2^bits equal-count bins; entry j =
+ * PER_ROW: the sorted row is cut into 2^bits equal-count bins; entry j =
  *   fp16(round-to-nearest-even of fp64(sum of bin j) / count); code =
  *   #{j : w > (L_j + L_{j+1}) / 2} (nearest entry, ties to the lower index).
- *   K <= 32768 (the row is sorted in LDS); larger K -> DQ_ERR_UNSUPPORTED.
+ *   K <= 32768 (a workgroup holds the row in registers); larger K ->
+ *   DQ_ERR_UNSUPPORTED.
  * PAPER_GRID (App. A "LUT formats"): grid = host pointer to 2^bits fp16
  *   values (ascending, one exactly 0) or NULL for the paper's grid rounded to
  *   fp16; G = fp32(max|W| / 2688); per block of 16 the largest |w| (lowest k
@@ -231,7 +232,10 @@ dq_status dq_quantize_act_nvfp4(const uint16_t* X, int64_t M, int64_t K, const f
  *   16 (rows 32j..32j+15 = gate rows 16j.., rows 32j+16..32j+31 = up rows
  *   16j..); the output column j = silu(gate_j) * up_j, N/2 columns.
  * K % 16 == 0, M >= 0, N >= 0; K < 2^23 (the kernel addresses a row panel of
- * each operand with 32-bit offsets; larger K -> DQ_ERR_UNSUPPORTED). */
+ * each operand with 32-bit offsets; larger K -> DQ_ERR_UNSUPPORTED).
+ * Sums are fp32.  Their order is fixed for given M, N and K (equal calls give
+ * equal bits) but changes with M: the last bits of a row may depend on how many
+ * rows the call has. */
 dq_status dq_prefill_gemm_workspace_size(int64_t M, int64_t K, size_t* bytes);
 dq_status dq_prefill_gemm(const dq_nvfp4_t* A, const uint16_t* X, const float* G_x_static,
                           const dq_nvfp4_t* W, int64_t M, int out_kind, void* Y,
@@ -272,14 +276,13 @@ dq_status dq_autocast_lut_to_nvfp4(const dq_lut_t* W, const float* G_override, c
  * y[b, n] = sum_k x[b, k] * w_hat[n, k], w_hat = e2m1 * e4m3(scale) * G.
  * x: device bf16 [B, K] row-major, 1 <= B <= 16.  W: NVFP4 weights as packed
  * by dq_pack_nvfp4 (rows = N, cols = K).  out_kind DQ_OUT_F32 / DQ_OUT_BF16:
- * y is device [B, N] row-major; x 16-byte aligned.  Small batches (B <= 8,
- * row tiles of 32 that fit one resident round of workgroups, B * K within
- * the staging limit) run in one launch that splits K inside each workgroup
- * and needs no workspace (dq_decode_gemv_nvfp4_workspace_size reports 0);
- * otherwise
- * workspace / workspace_bytes are as for dq_decode_gemv (partial sums over K
- * groups, where a row is split over workgroups; NULL takes stream-ordered
- * memory from the library's pool).
+ * y is device [B, N] row-major; x 16-byte aligned.  workspace /
+ * workspace_bytes are as for dq_decode_gemv (partial sums over K groups, where
+ * a row is split over workgroups; NULL takes stream-ordered memory from the
+ * library's pool).  Small calls (B <= 8, row tiles of 32 that fit one resident
+ * round of workgroups, B * K within 48 KiB of fp16 per workgroup) are one
+ * launch and need no workspace (dq_decode_gemv_nvfp4_workspace_size reports
+ * 0).
  * Activations are used as fp16 after a power-of-two rescale per batch row
  * and K slice (the conversion described for dq_decode_gemv); weight products
  * are exact, sums fp32. */

@@ -222,7 +222,7 @@ dq_status dq_pack_lut3(const float* W, int64_t N, int64_t K, int bits, int mode,
   if (out->rows != N || out->cols != K || out->bits != bits || out->mode != mode)
     return fail(DQ_ERR_INVALID_ARG, "out descriptor does not match N, K, bits, mode");
   if (mode == DQ_LUT_PER_ROW && K > 32768)
-    return fail(DQ_ERR_UNSUPPORTED, "PER_ROW packing sorts a row in LDS: K <= 32768");
+    return fail(DQ_ERR_UNSUPPORTED, "PER_ROW packing holds a row in registers: K <= 32768");
   if (mode == DQ_LUT_PER_ROW && K == 0 && N > 0)
     return fail(DQ_ERR_INVALID_ARG, "PER_ROW needs K > 0 (bin means of empty rows are undefined)");
   if (mode == DQ_LUT_PAPER_GRID && grid != nullptr) {

@@ -234,19 +234,16 @@ __global__ __launch_bounds__(256) void nvfp4_gemv_kernel(const uint16_t* __restr
   if (q < cycles) consume(q, cb0);
 }
 
-// One-launch kernel for small batches (the staged slices within 48 KiB of LDS;
-// see ks_better) and at most one resident round of row tiles (16 wavefronts
-// per compute unit).  A workgroup of kKsWaves (4 or 8) wavefronts takes one
-// row tile;
-// wavefront w takes K steps [w SPW, (w + 1) SPW).  It copies its own slice of
-// x straight into LDS (issued before its code loads, so the copy is not
-// queued behind them), then per batch row takes the slice maximum, a
-// power-of-two scale and converts in place (no barrier: nothing is shared),
-// streams its codes in cycles of kCyc steps, and parks its unscaled partial
-// sums in LDS.  After the one barrier, the kKsWaves partials of each (batch
-// row, tile row) are added in wavefront order and stored (deterministic).
-
-
+// One-launch kernel for small batches where it is the faster (see ks_better),
+// the staged slices within 48 KiB of LDS and at most one resident round of row
+// tiles (16 wavefronts per compute unit).  A workgroup of kKsWaves (4 or 8)
+// wavefronts takes one row tile; wavefront w takes K steps [w SPW, (w + 1) SPW).
+// It copies its own slice of x straight into LDS (issued before its code loads,
+// so the copy is not queued behind them), then per batch row takes the slice
+// maximum, a power-of-two scale and converts in place (no barrier: nothing is
+// shared), streams its codes in cycles of kCyc steps, and parks its unscaled
+// partial sums in LDS.  After the one barrier, the kKsWaves partials of each
+// (batch row, tile row) are added in wavefront order and stored (deterministic).
 template <int kKsWaves>
 __global__ __launch_bounds__(64 * kKsWaves) void nvfp4_gemv_ks_kernel(
     const uint16_t* __restrict__ x, int B, int64_t K, const uint8_t* __restrict__ codes,
@@ -494,8 +491,9 @@ bool ks_better(int64_t B, int64_t N, int64_t K) {
 
 }  // namespace
 
-// (the size that callers query: what nvfp4_gemv_kernel needs; the batched
-// kernel takes no more K groups than fit in it)
+// The size that callers query and keep: what nvfp4_gemv_kernel needs, and none
+// where the one-launch kernel fits, also where the batched kernel is the faster
+// and runs; it takes no more K groups than fit in this (one, or passes, in 0).
 size_t gemv_nvfp4_workspace_bytes(int64_t B, int64_t N, int64_t K) {
   if (B < 1 || N == 0 || K == 0 || ks_plan(B, N, K).ok) return 0;
   return nv_plan(B, N, K).partial_bytes;
