@@ -581,10 +581,11 @@ __global__ __launch_bounds__(Gm::threads, Gm::occ) void nvfp4_gemm_kernel(
 // multiplies as above; the S partial tiles are then added in wavefront order
 // through LDS, RB blocks at a time, one wavefront per block.
 // Bound: MFMA issue with the dequantization beside it (a 64 x 64 wavefront
-// tile issues 8.5 VALU instructions per MFMA; a probe shows about four hidden
-// behind each MFMA and the others costing 3 cycles), and at the smallest M the
-// weight stream.  The tile (choose_short) is picked so that the compute units
-// are evenly loaded.  No scratch memory: the split stays inside the workgroup.
+// tile issues 9.3 VALU instructions per MFMA, a 96 x 64 one 8.1 by the counters;
+// a probe shows about four hidden behind each MFMA and the others costing 3
+// cycles), and at the smallest M the weight stream.  The tile (choose_short) is
+// picked so that the compute units are evenly loaded.  No scratch memory: the
+// split stays inside the workgroup.
 // Measured beside it: deeper register rings (within 3 %), eight wavefronts
 // against four of the same tile (within 5 %), dequantizing a whole sub-step
 // ahead of its MFMAs instead of between them (5-15 % slower).

@@ -685,9 +685,9 @@ constexpr int kRingMulti = 8;
 // parking only the columns that are used (all sixteen lanes' before) lets a
 // compute unit convert x once: LUT3 65536 x 17408 at batch 2 108 -> 95 us,
 // 49168 x 8192 43.6 -> 36.5.
-// Bound: VALU issue of the lookups (about 54 instructions per 2048-code chunk)
+// Bound: VALU issue of the lookups (59 instructions per 2048-code chunk counted)
 // with the code stream beside it, and at the small matrices the launch, one
-// memory round trip and the conversion (350 instructions a wavefront at three
+// memory round trip and the conversion (390 instructions a wavefront at three
 // chunks and batch 16, about 2 us), which every compute unit does for all of
 // x.  Against the kernel before it (K groups staged in LDS by every workgroup,
 // two barriers, a reduction launch for each matrix): 27B block, LUT3, batch 2

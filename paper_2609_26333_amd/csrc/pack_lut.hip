@@ -126,7 +126,7 @@ __device__ inline void store_group(uint8_t* codes, int64_t row, int64_t group, i
 //  4. codes by comparison with the midpoints rounded down to fp32 (for an
 //     fp32 w the same as the exact fp64 comparison), eight lanes combining
 //     their four codes each into a 32-code group.
-// Bound: the VALU (about 78 instructions per value) and the LDS accesses
+// Bound: the VALU (77 instructions per value counted) and the LDS accesses
 // beside it; the row is read once.  A bitonic sort of the row in LDS (78
 // passes at K = 4096) took 1417 us for 12288 x 4096, this takes 154
 // (1.4 TB/s).  Thresholds by comparison for every value, four wavefronts per
